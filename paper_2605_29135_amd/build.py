@@ -9,7 +9,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmoe_budget.so")
-SOURCES = ["kernels.hip", "prefill.hip", "attention.hip", "residency.cpp", "residency_dev.hip", "capi.cpp", "stack.cpp",
+SOURCES = ["kernels.hip", "batch_ffn.hip", "prefill.hip", "attention.hip", "residency.cpp", "residency_dev.hip", "capi.cpp", "stack.cpp",
            "analysis.cpp"]
 # Host-only sources (the host tier's CPU GEMVs): built by the host compiler, then linked into the library.
 HOST_SOURCES = ["host_ffn.cpp"]

@@ -1,0 +1,505 @@
+// batch_ffn.hip -- the expert FFN of 2 to 16 decode tokens on the matrix cores (gfx950).
+//
+// A decode batch is bound by the bytes of the distinct experts that it selects (61 on average for 16
+// tokens of top-8 over 256 Zipf-routed experts: 384 MB of bf16).  A weight tile is loaded once, straight
+// into registers in the matrix-core lane layout, and multiplied with all of its expert's tokens at once,
+// so that a wave has nothing to do per token and its loads stay in flight.
+#include "internal.h"
+#include "device_common.h"
+
+namespace moe {
+namespace {
+
+using namespace dev;
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kMaxPairs = MOE_MAX_DECODE_TOKENS * MOE_MAX_TOPK;  // (token, rank) pairs of a call
+
+// High halves of two floats as a bf16 pair (lo's in the low half).
+__device__ __forceinline__ uint32_t high_halves(float lo, float hi) {
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+// Eight fp32 values -> three bf16x8 terms whose sum is exact: each term takes the top 8 significant bits
+// of what the terms before it leave (truncation: no finite value overflows, and 24 bits take three terms).
+// PAIRS: the order 0,4,1,5,2,6,3,7 (int4 weights).
+template <bool PAIRS>
+__device__ __forceinline__ void split3(const float *v, bf16x8 &t1, bf16x8 &t2, bf16x8 &t3) {
+    uint32_t a[4], b[4], c[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float x0 = v[PAIRS ? e : 2 * e], x1 = v[PAIRS ? e + 4 : 2 * e + 1];
+        a[e] = high_halves(x0, x1);
+        const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & 0xffff0000u);
+        const float r1 = x1 - __uint_as_float(__float_as_uint(x1) & 0xffff0000u);
+        b[e] = high_halves(r0, r1);
+        const float q0 = r0 - __uint_as_float(__float_as_uint(r0) & 0xffff0000u);
+        const float q1 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+        c[e] = high_halves(q0, q1);
+    }
+    t1 = __builtin_bit_cast(bf16x8, make_uint4(a[0], a[1], a[2], a[3]));
+    t2 = __builtin_bit_cast(bf16x8, make_uint4(b[0], b[1], b[2], b[3]));
+    t3 = __builtin_bit_cast(bf16x8, make_uint4(c[0], c[1], c[2], c[3]));
+}
+
+// The eight signed nibbles q of a dword as bf16 24 + q (exact), in the order 0,4,1,5,2,6,3,7: a nibble shifted
+// to the top of the mantissa of 16, its sign bit flipped, is 16 + (q + 8).  One shift and one three-input bit
+// operation per two weights (the conversion instruction for a nibble took half of the kernel's time).  The
+// sums start from -24 times the sum of the other factors instead of zero.
+constexpr uint32_t kMinusBias2 = 0xc1c0c1c0u;  // two bf16 -24
+__device__ __forceinline__ bf16x8 nibbles_biased(uint32_t v) {
+    constexpr uint32_t m = 0x00780078u, f = 0x41c041c0u;
+    return __builtin_bit_cast(bf16x8, make_uint4(((v << 3) & m) ^ f, ((v >> 1) & m) ^ f, ((v >> 5) & m) ^ f,
+                                                 ((v >> 9) & m) ^ f));
+}
+
+// How a block walks an expert's gate/up matrix.  A step is one 16-byte weight load per lane and 16-row tile:
+// lane (lr = l % 16, lg = l / 16) holds row lr, elements STEP / 4 * lg onward of the step, and the same
+// elements of token lr.  An item is TILES tiles of one expert; its eight waves take contiguous shares of the
+// steps, CS (at most MAXS) of them at a time in registers.  CHAINS: independent fp32 sums of the leading
+// products, so that a chain of roundings is no longer than a lane's in a row-wise dot product.
+template <int DT> struct Walk;
+template <> struct Walk<BF16> { static constexpr int STEP = 32, TILES = 1, MAXS = 8, CHAINS = 2; };
+template <> struct Walk<INT4> { static constexpr int STEP = 128, TILES = 2, MAXS = 2, CHAINS = 1; };
+
+constexpr int kBatchWaves = 8, kBatchBlock = kBatchWaves * kWave;
+constexpr int kBatchGrid = 256;  // one persistent block per compute unit
+
+// The call's experts, found by every block for itself (no launch groups the pairs first): group n's blob as a
+// byte offset from `pool` and its key; each pair's key (-1: a pair that contributes nothing).  A group holds
+// at most 16 pairs: an expert has more only where tokens name it twice, and then takes several groups.
+struct BatchGroups {
+    int n;
+    long long off[kMaxPairs + 1];
+    int group_key[kMaxPairs + 1];  // -1: the shared expert's group (every token)
+    int key[kMaxPairs];            // 16 * expert + (the pair's rank among its expert's pairs) / 16
+    int ids[kMaxPairs];
+    float weight[kMaxPairs];
+    int per_wave[kMaxPairs / kWave];
+};
+
+__device__ __forceinline__ void find_groups(BatchGroups &G, int P, int E, const int32_t *__restrict__ ids,
+                                            const int32_t *__restrict__ slot_of, const float *__restrict__ weights,
+                                            const uint8_t *pool, size_t expert_bytes, const uint8_t *shared_w, int *err) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    int e = -1, s = -1;
+    if (tid < kMaxPairs) {
+        float w = 0.f;
+        if (tid < P) {
+            e = ids[tid];
+            w = weights[tid];
+        }
+        const bool in = e >= 0 && e < E;
+        G.ids[tid] = in ? e : -1;
+        G.weight[tid] = w;
+        if (in) s = slot_of ? slot_of[e] : e;
+        if (tid < P && blockIdx.x == 0) {
+            if (!in) atomicOr(err, kErrRange);
+            else if (s < 0) atomicOr(err, kErrNotResident);
+        }
+    }
+    __syncthreads();
+    bool first = false;
+    int key = -1;
+    unsigned long long firsts = 0;
+    if (tid < kMaxPairs) {
+        int rank = 0;
+        const int4 *v = reinterpret_cast<const int4 *>(G.ids);
+        const int nq = min(P, (wave + 1) * kWave);  // (the pairs before any of this wave's)
+        for (int q = 0; q < nq; q += 4) {
+            const int4 o = v[q / 4];
+            rank += (o.x == e && q < tid) + (o.y == e && q + 1 < tid) + (o.z == e && q + 2 < tid) + (o.w == e && q + 3 < tid);
+        }
+        if (s >= 0) key = 16 * e + rank / 16;
+        G.key[tid] = key;
+        first = s >= 0 && rank % 16 == 0;
+        firsts = __ballot(first);
+        if (lane == 0) G.per_wave[wave] = __popcll(firsts);
+    }
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kMaxPairs / kWave; ++w) {
+        before += w < wave ? G.per_wave[w] : 0;
+        all += G.per_wave[w];
+    }
+    if (first) {
+        const int n = before + __popcll(firsts & ((1ull << lane) - 1ull));
+        G.off[n] = (long long)s * (long long)expert_bytes;
+        G.group_key[n] = key;
+    }
+    if (tid == 0) {
+        G.n = all + (shared_w != nullptr);
+        if (shared_w) {
+            G.off[all] = (long long)(shared_w - pool);
+            G.group_key[all] = -1;
+        }
+    }
+    __syncthreads();
+}
+
+// act[p, i] = w_p * silu(W_g[i] . x_t) * (W_u[i] . x_t) for every (token, rank) pair p and the shared expert.
+// Each block takes a contiguous share of the (expert, row tiles) items and streams their weights: the next
+// item's are in flight while this one is multiplied, and the expert's tokens stay in registers from item to
+// item.  The waves' partial products are added through LDS in wave order.  The weights (int4: as bf16 24 + q,
+// the scale applied to each quantisation group's fp32 sum) meet the tokens' values as three bf16 terms, so
+// that every product is exact and only the order of the fp32 sums differs from a row-wise dot product.
+// Bound by HBM (large batches) or by the latency of a few items per block (small ones).  Measured against one
+// wave per row pair that took its expert's tokens one after the other, behind a launch that grouped the pairs:
+// 16 tokens, H 2048, I 512, 256 Zipf-routed bf16 experts + shared (260 MB): 54 + 16 -> 56 us, 4.6 TB/s; 5
+// tokens on int4 experts of the same shape (31 MB): 31 + 6 -> 18 us.
+template <int DT, int CS, bool ONE>  // ONE: a single pass over the reduction range
+__global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
+    const float *__restrict__ x, int T, int H, int I, int E, int k, const int32_t *__restrict__ ids,
+    const int32_t *__restrict__ slot_of, const uint8_t *__restrict__ pool, size_t expert_bytes,
+    const uint8_t *__restrict__ shared_w, const float *__restrict__ weights, float *__restrict__ act, int *err) {
+    using W = Walk<DT>;
+    constexpr int MT = W::TILES, XV = W::STEP / 4, CH = W::CHAINS;  // XV: fp32 values per lane and step
+    constexpr int SUB = DT == INT4 ? 4 : 1;                         // matrix products per step and term
+    __shared__ float red[2][kBatchWaves][MT][4][kWave];
+    __shared__ BatchGroups G;
+    __shared__ int members[kBatchWaves][kMaxPairs];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lr = lane % 16, lg = lane / 16;
+    const int P = T * k;
+    find_groups(G, P, E, ids, slot_of, weights, pool, expert_bytes, shared_w, err);
+
+    int *mem = members[wave];  // the pairs of the expert at hand, ascending
+    const int tiles = 2 * I / (16 * MT);
+    const int items = G.n * tiles;
+    const int it0 = int((long long)items * blockIdx.x / gridDim.x), it1 = int((long long)items * (blockIdx.x + 1) / gridDim.x);
+    if (it0 >= it1) return;
+    const int steps = H / W::STEP;
+    const int chunks = ONE ? 1 : (steps + kBatchWaves * CS - 1) / (kBatchWaves * CS);  // passes over the reduction range
+    const int share = (steps + kBatchWaves * chunks - 1) / (kBatchWaves * chunks);  // steps per wave and pass, <= CS
+    const size_t rb = row_bytes_of(DT, H);
+    const int KG = H / 128;
+
+    struct Weights {
+        uint4 w[CS][MT];
+        uint32_t sc[DT == INT4 ? CS : 1][MT];
+    } b0, b1;
+    struct Unit {  // one pass over one item
+        int it, g, tile, c;
+    };
+    auto next_unit = [&](Unit u) {
+        if (++u.c == chunks) {
+            u.c = 0;
+            ++u.it;
+            if (++u.tile == tiles) {
+                u.tile = 0;
+                ++u.g;
+            }
+        }
+        return u;
+    };
+    // This wave's steps of pass c: [first, first + live)
+    auto first_step = [&](int c) { return (c * kBatchWaves + wave) * share; };
+    // (No branch around these loads, and no other load between them and their use: they are counted, and a
+    // wait for one item's weights leaves the next one's in flight.  Past the block's last unit they all read
+    // one line.)
+    auto load = [&](Weights &b, const Unit &u) __attribute__((always_inline)) {
+        const bool more = u.it < it1;
+        const int row0 = u.tile * 16 * MT, s0 = first_step(u.c);
+        const uint8_t *blob = pool + (more ? G.off[u.g] : 0);
+        const size_t row = more ? size_t(row0 + lr) : 0;
+        const uint8_t *wrow = blob + row * rb + 16 * lg;
+        const uint16_t *srow = reinterpret_cast<const uint16_t *>(blob + (more ? size_t(I) * H : 0)) + row * KG;
+        const size_t wt = more ? 16 * rb : 0, st = more ? 16 * KG : 0;  // from tile to tile
+        const int last = more ? steps - 1 : 0;
+#pragma unroll
+        for (int r = 0; r < CS; ++r) {
+            const int s = min(s0 + r, last);  // (past the end: loaded, not multiplied)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                b.w[r][j] = load16_stream(wrow + j * wt + size_t(s) * 64);
+                if constexpr (DT == INT4) b.sc[r][j] = srow[j * st + s];
+            }
+        }
+    };
+
+    bf16x8 xt[CS][SUB][3];
+    floatx4 hi0[DT == INT4 ? CS : 1], lo0[DT == INT4 ? CS : 1];  // int4: -24 times the tokens' group sums
+    floatx4 lead[CH][MT], tail[MT];
+    int cnt = 0, g_at = -1;
+    auto process = [&](Weights &b, const Unit &u, Weights &next, const Unit &un) __attribute__((always_inline)) {
+        const int it = u.it, c = u.c, g = u.g;
+        const int row0 = u.tile * 16 * MT, s0 = first_step(c), live = min(share, steps - s0);
+        const bool fresh = g != g_at;
+        if (fresh) {
+            g_at = g;
+            const int gk = G.group_key[g];
+            if (gk < 0) {
+                cnt = T;
+                if (lane < T) mem[lane] = P + lane;
+            } else {
+                cnt = 0;
+#pragma unroll
+                for (int m = 0; m < kMaxPairs / kWave; ++m) {
+                    const int p = m * kWave + lane;
+                    const unsigned long long mask = __ballot(G.key[p] == gk);
+                    if (mask >> lane & 1ull) mem[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = p;
+                    cnt += __popcll(mask);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        }
+        if (fresh || chunks > 1) {
+            // the tokens' values of this wave's steps (columns past the last token repeat it and are not stored;
+            // steps past the wave's share take zeros)
+            const int p = mem[min(lr, cnt - 1)];
+            const float *xrow = x + size_t(p < P ? p / k : p - P) * H + XV * lg;
+            float4 raw[CS][XV / 4];
+#pragma unroll
+            for (int r = 0; r < CS; ++r)
+#pragma unroll
+                for (int q = 0; q < XV / 4; ++q)
+                    raw[r][q] = load_f4(reinterpret_cast<const float4 *>(xrow + size_t(min(s0 + r, steps - 1)) * W::STEP) + q);
+#pragma unroll
+            for (int r = 0; r < CS; ++r) {
+                const uint32_t keep = r < live ? ~0u : 0u;
+#pragma unroll
+                for (int q = 0; q < XV / 4; ++q) {
+                    float4 &f = raw[r][q];
+                    f = make_float4(__uint_as_float(__float_as_uint(f.x) & keep), __uint_as_float(__float_as_uint(f.y) & keep),
+                                    __uint_as_float(__float_as_uint(f.z) & keep), __uint_as_float(__float_as_uint(f.w) & keep));
+                }
+#pragma unroll
+                for (int d = 0; d < SUB; ++d) {
+                    const float4 a = raw[r][2 * d], bq = raw[r][2 * d + 1];
+                    const float v[8] = {a.x, a.y, a.z, a.w, bq.x, bq.y, bq.z, bq.w};
+                    split3<DT == INT4>(v, xt[r][d][0], xt[r][d][1], xt[r][d][2]);
+                }
+                if constexpr (DT == INT4) {
+                    const bf16x8 m = __builtin_bit_cast(bf16x8, make_uint4(kMinusBias2, kMinusBias2, kMinusBias2, kMinusBias2));
+                    hi0[r] = lo0[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int d = 0; d < SUB; ++d) {
+                        hi0[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][0], m, hi0[r], 0, 0, 0);
+                        lo0[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][2], m, lo0[r], 0, 0, 0);
+                        lo0[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][1], m, lo0[r], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        load(next, un);
+        // (the weights at hand pass through an empty asm after the next item's loads: those are all issued first)
+#pragma unroll
+        for (int r = 0; r < CS; ++r)
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                u32x4 v = {b.w[r][j].x, b.w[r][j].y, b.w[r][j].z, b.w[r][j].w};
+                asm volatile("" : "+v"(v)::"memory");
+                b.w[r][j] = make_uint4(v.x, v.y, v.z, v.w);
+            }
+        if (c == 0) {
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                tail[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int h = 0; h < CH; ++h) lead[h][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < CS; ++r) {
+#pragma unroll
+            for (int j = 0; j < MT; ++j) {
+                const uint32_t wv[4] = {b.w[r][j].x, b.w[r][j].y, b.w[r][j].z, b.w[r][j].w};
+                if constexpr (DT == BF16) {
+                    const bf16x8 w = __builtin_bit_cast(bf16x8, b.w[r][j]);
+                    tail[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][0][2], w, tail[j], 0, 0, 0);
+                    lead[r % CH][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][0][0], w, lead[r % CH][j], 0, 0, 0);
+                    tail[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][0][1], w, tail[j], 0, 0, 0);
+                } else {
+                    floatx4 hi = hi0[r], lo = lo0[r];
+#pragma unroll
+                    for (int d = 0; d < SUB; ++d) {
+                        const bf16x8 w = nibbles_biased(wv[d]);
+                        lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][2], w, lo, 0, 0, 0);
+                        hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][0], w, hi, 0, 0, 0);
+                        lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][1], w, lo, 0, 0, 0);
+                    }
+                    const float sc = bf16_bits_to_float(b.sc[r][j]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) lead[0][j][q] = fmaf(sc, hi[q] + lo[q], lead[0][j][q]);
+                }
+            }
+        }
+        if (c + 1 < chunks) return;
+        // lane holds C[token 4 lg + q][row lr] of each tile; two buffers, so that one barrier per item suffices
+        auto &rd = red[it & 1];
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v = tail[j][q];
+#pragma unroll
+                for (int h = CH / 2; h > 0; h /= 2)
+#pragma unroll
+                    for (int i = 0; i < h; ++i) lead[i][j][q] += lead[i + h][j][q];
+                rd[wave][j][q][lane] = v + lead[0][j][q];
+            }
+        __syncthreads();
+        // 8 activations per tile and token: gate row 2i and up row 2i + 1
+        const int i = tid % (8 * MT), col = tid / (8 * MT);
+        if (col < cnt && col < 16) {
+            const int j = i / 8, q = col % 4, l = 16 * (col / 4) + 2 * (i % 8);
+            float gate = 0.f, up = 0.f;
+#pragma unroll
+            for (int w = 0; w < kBatchWaves; ++w) {
+                gate += rd[w][j][q][l];
+                up += rd[w][j][q][l + 1];
+            }
+            const int p = mem[col];
+            const float wp = p < P ? G.weight[p] : 1.f;
+            act[size_t(p) * I + row0 / 2 + i] = wp * (gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate)) * up);
+        }
+    };
+    Unit ua = {it0, it0 / tiles, it0 % tiles, 0};
+    load(b0, ua);
+    while (ua.it < it1) {
+        const Unit ub = next_unit(ua);
+        process(b0, ua, b1, ub);
+        ua = next_unit(ub);
+        if (ub.it < it1) process(b1, ub, b0, ua);
+    }
+}
+
+// fp32 experts: one wave per row pair (gate row 2i, up row 2i + 1), its weights loaded once and applied to each
+// token of the expert (fp32 matrix instructions measured no faster here, and their longer chains of roundings
+// less exact).  Block (row pairs, p): for all the pairs of pair p's expert if p is the first of them (the
+// other blocks leave: each wave finds the expert's pairs by ballots over the ids, so that no launch groups
+// them first: 5.3 us of the 31.8 us of 7 tokens at H 1408, I 384); p = T * k is the shared expert.
+template <int NCH, bool FULL>
+__global__ __launch_bounds__(kBlock) void batch_gateup_f32_kernel(
+    const float *__restrict__ x, int T, int H, int I, int E, int k, const int32_t *__restrict__ ids,
+    const int32_t *__restrict__ slot_of, const uint8_t *__restrict__ pool, size_t expert_bytes,
+    const uint8_t *__restrict__ shared_w, const float *__restrict__ weights, float *__restrict__ act, int *err) {
+    constexpr int EPC = Fmt<F32>::EPC;
+    __shared__ int members[kBlock / kWave][kMaxPairs];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int g = blockIdx.y, P = T * k;
+    int *mem = members[wave];  // the expert's pairs, ascending
+    int cnt;
+    const uint8_t *blob;
+    if (g < P) {
+        int id[kMaxPairs / kWave];
+#pragma unroll
+        for (int m = 0; m < kMaxPairs / kWave; ++m) id[m] = ids[min(m * kWave + lane, P - 1)];
+        int e = 0;
+#pragma unroll
+        for (int m = 0; m < kMaxPairs / kWave; ++m)
+            if (g / kWave == m) e = __builtin_amdgcn_readlane(id[m], g % kWave);
+        if (e < 0 || e >= E) {
+            if (blockIdx.x == 0 && tid == 0) atomicOr(err, kErrRange);
+            return;
+        }
+        const int s = slot_of ? load_stream_word(slot_of + e) : e;
+        cnt = 0;
+        bool first = true;
+#pragma unroll
+        for (int m = 0; m < kMaxPairs / kWave; ++m) {
+            const int p = m * kWave + lane;
+            const unsigned long long mask = __ballot(p < P && id[m] == e);
+            if (mask >> lane & 1ull) mem[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = p;
+            if (cnt == 0 && mask) first = m * kWave + int(__builtin_ctzll(mask)) == g;
+            cnt += __popcll(mask);
+        }
+        if (s < 0) {
+            if (blockIdx.x == 0 && tid == 0) atomicOr(err, kErrNotResident);
+            return;
+        }
+        if (!first) return;
+        blob = pool + size_t(s) * expert_bytes;
+    } else {
+        cnt = T;
+        if (lane < T) mem[lane] = P + lane;
+        blob = shared_w;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int i = blockIdx.x * (kBlock / kWave) + wave;
+    if (i >= I) return;
+    const size_t rb = row_bytes_of(F32, H);
+    const uint8_t *gate = blob + size_t(2 * i) * rb + 16 * lane;
+    float xv[NCH][EPC];
+    auto load_token = [&](int p) {
+        const float *xt = x + size_t(p < P ? p / k : p - P) * H;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int col0 = (c * kWave + lane) * EPC;
+            if (FULL || col0 < H) {
+                load_x<F32>(xt, col0, xv[c]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < EPC; ++q) xv[c][q] = 0.f;
+            }
+        }
+    };
+    load_token(mem[0]);  // before the weights: loads retire in order, so waiting for x never waits for them
+    uint4 wg[NCH], wu[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const bool in = FULL || (c * kWave + lane) * EPC < H;
+        wg[c] = in ? load16_stream(gate + size_t(c) * 16 * kWave) : make_uint4(0, 0, 0, 0);
+        wu[c] = in ? load16_stream(gate + rb + size_t(c) * 16 * kWave) : make_uint4(0, 0, 0, 0);
+    }
+    for (int q = 0; q < cnt; ++q) {
+        const int p = mem[q];
+        if (q > 0) load_token(p);
+        const float wp = p < P ? weights[p] : 1.f;
+        float ga = 0.f, ua = 0.f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            ga += chunk_dot<F32>(wg[c], xv[c]);
+            ua += chunk_dot<F32>(wu[c], xv[c]);
+        }
+        ga = wave_sum(ga);
+        ua = wave_sum(ua);
+        if (lane == 0) act[size_t(p) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
+    }
+}
+
+}  // namespace
+
+hipError_t launch_batch_gateup(const float *x, int T, int H, int I, int E, int k, const int32_t *ids,
+                               const float *weights, const int32_t *slot_of, const uint8_t *pool, size_t expert_bytes,
+                               int dtype, const uint8_t *shared_w, float *act, int *err, hipStream_t s) {
+    if (T < 2 || T > MOE_MAX_DECODE_TOKENS || k < 1 || k > MOE_MAX_TOPK || H % 128 || I % 128) return hipErrorInvalidValue;
+#define GU_LAUNCH(DT, CS, ONE)                                                                                 \
+    {                                                                                                          \
+        batch_gateup_kernel<DT, CS, ONE><<<kBatchGrid, kBatchBlock, 0, s>>>(x, T, H, I, E, k, ids, slot_of, pool,   \
+                                                                       expert_bytes, shared_w, weights, act, err); \
+        return hipGetLastError();                                                                              \
+    }
+    // the fewest steps per wave that hold a wave's share of the reduction range (longer ranges take passes)
+#define GU_CASE(DT)                                                                       \
+    if (dtype == DT) {                                                                    \
+        const int share = (H / Walk<DT>::STEP + kBatchWaves - 1) / kBatchWaves;           \
+        if (share <= Walk<DT>::MAXS / 2) GU_LAUNCH(DT, Walk<DT>::MAXS / 2, true)          \
+        if (share <= Walk<DT>::MAXS) GU_LAUNCH(DT, Walk<DT>::MAXS, true)                  \
+        GU_LAUNCH(DT, Walk<DT>::MAXS, false)                                                  \
+    }
+    GU_CASE(BF16) GU_CASE(INT4)
+#undef GU_CASE
+#undef GU_LAUNCH
+    if (dtype != F32) return hipErrorInvalidValue;
+    const dim3 grid(unsigned((I + kBlock / kWave - 1) / (kBlock / kWave)), unsigned(T * k + (shared_w ? 1 : 0)));
+    // FULL: every lane's chunk slots lie inside the row, no bound checks
+#define F32_CASE(N)                                                                                                  \
+    if (H <= N * kWave * Fmt<F32>::EPC) {                                                                            \
+        auto *kernel = H == N * kWave * Fmt<F32>::EPC ? batch_gateup_f32_kernel<N, true> : batch_gateup_f32_kernel<N, false>; \
+        kernel<<<grid, kBlock, 0, s>>>(x, T, H, I, E, k, ids, slot_of, pool, expert_bytes, shared_w, weights, act, err); \
+        return hipGetLastError();                                                                                    \
+    }
+    F32_CASE(1) F32_CASE(2) F32_CASE(4) F32_CASE(8)
+#undef F32_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace moe

@@ -21,7 +21,6 @@ size_t down_offset(int H, int I, int dtype);
 // Workspace carve-up of moe_expert_ffn_grouped.
 struct FfnWorkspace {
     float *act;       // [(T*k + T) x I] SwiGLU activations, one row per (token, rank) pair + shared
-    int *groups;      // grouping table (T > 1 only)
 };
 size_t ffn_workspace_bytes(int T, int k, int I);
 FfnWorkspace ffn_workspace(void *base, int T, int k, int I);
@@ -44,7 +43,7 @@ hipError_t launch_topk_softmax(const float *logits, int T, int E, int k, int32_t
 // x[i] += y[i], i < n (y may be host memory: the host tier's output).
 hipError_t launch_add(float *x, const float *y, int n, hipStream_t s);
 
-// Which expert kernels launch_expert_ffn enqueues (grouping goes with gate/up).
+// Which expert kernels launch_expert_ffn enqueues.
 enum : int { kFfnGateUp = 1, kFfnDown = 2, kFfnBoth = 3 };
 
 // A single-token step's missing experts streamed in by its gate/up launch
@@ -83,6 +82,10 @@ hipError_t launch_expert_ffn(const float *x, int T, int H, int I, int E, int k, 
                              size_t expert_bytes, int dtype, const void *shared_w, float *y,
                              bool accumulate, const FfnWorkspace &ws, int *err_flags, hipStream_t s,
                              const FfnPlan *plan = nullptr, int parts = kFfnBoth);
+// The gate/up half of launch_expert_ffn for 2 to 16 tokens (batch_ffn.hip).
+hipError_t launch_batch_gateup(const float *x, int T, int H, int I, int E, int k, const int32_t *ids,
+                               const float *weights, const int32_t *slot_of, const uint8_t *pool, size_t expert_bytes,
+                               int dtype, const uint8_t *shared_w, float *act, int *err, hipStream_t s);
 hipError_t launch_combine(const float *y_partial, const float *weights, const float *y_shared, int T,
                           int k, int H, float *y, bool accumulate, hipStream_t s);
 hipError_t launch_slot_update(int32_t *table, const int32_t *index, const int32_t *value, int n,

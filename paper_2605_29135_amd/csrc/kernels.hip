@@ -426,89 +426,6 @@ __global__ __launch_bounds__(kRouterKWaves * kWave) void router_mfma_kernel(cons
     if (t < T && e < E) logits[size_t(t) * E + e] = v + (bias ? bias[size_t(t) * E + e] : 0.f);
 }
 
-// ------------------------------------------------------------- grouping ---
-// Group table in the workspace (int32):
-//   [0] groups (routed + shared)  [1] routed groups  [2] valid routed pairs  [3] unused
-//   slot[G] start[G] count[G] pairs[P + T]     with G = T*k + 1, P = T*k
-// Pair p = t*k + j is (token t, rank j); the shared expert's pairs are P + t.
-// Groups list the distinct valid experts in ascending id; a group's pairs
-// are ascending.  slot -2 marks the shared expert's group.
-__device__ __forceinline__ int *group_slot(int *g, int T, int k) { return g + 4; }
-__device__ __forceinline__ int *group_start(int *g, int T, int k) { return g + 4 + (T * k + 1); }
-__device__ __forceinline__ int *group_count(int *g, int T, int k) { return g + 4 + 2 * (T * k + 1); }
-__device__ __forceinline__ int *group_pairs(int *g, int T, int k) { return g + 4 + 3 * (T * k + 1); }
-
-__global__ __launch_bounds__(kBlock) void group_pairs_kernel(const int32_t *__restrict__ ids, int T,
-                                                             int k, int E,
-                                                             const int32_t *__restrict__ slot_of,
-                                                             int has_shared, int *groups, int *err) {
-    __shared__ int e_eff[kBlock], s_eff[kBlock], first[kBlock];
-    const int P = T * k;  // <= 256
-    const int tid = threadIdx.x;
-    int e = -1, s = -1;
-    if (tid < P) {
-        e = ids[tid];
-        if (e < 0 || e >= E) {
-            atomicOr(err, kErrRange);
-            e = -1;
-        } else {
-            s = slot_of ? slot_of[e] : e;
-            if (s < 0) {
-                atomicOr(err, kErrNotResident);
-                e = -1;
-            }
-        }
-    }
-    e_eff[tid] = e;
-    s_eff[tid] = s;
-    __syncthreads();
-    int is_first = 0, rank = 0;
-    if (e >= 0) {
-        is_first = 1;
-        for (int q = 0; q < P; ++q) {
-            const int eq = e_eff[q];
-            if (eq < 0) continue;
-            if (eq == e && q < tid) is_first = 0;
-            if (eq < e || (eq == e && q < tid)) ++rank;
-        }
-    }
-    first[tid] = is_first;
-    __syncthreads();
-    int *gs = group_slot(groups, T, k), *gst = group_start(groups, T, k), *gc = group_count(groups, T, k);
-    int *gp = group_pairs(groups, T, k);
-    if (e >= 0) {
-        gp[rank] = tid;
-        if (is_first) {
-            int gidx = 0, cnt = 0;
-            for (int q = 0; q < P; ++q) {
-                if (first[q] && e_eff[q] < e) ++gidx;
-                if (e_eff[q] == e) ++cnt;
-            }
-            gs[gidx] = s;
-            gst[gidx] = rank;
-            gc[gidx] = cnt;
-        }
-    }
-    if (tid == 0) {
-        int ng = 0, nv = 0;
-        for (int q = 0; q < P; ++q) {
-            ng += first[q];
-            nv += e_eff[q] >= 0;
-        }
-        int total = ng;
-        if (has_shared) {
-            gs[ng] = -2;
-            gst[ng] = nv;
-            gc[ng] = T;
-            for (int t = 0; t < T; ++t) gp[nv + t] = P + t;
-            total = ng + 1;
-        }
-        groups[0] = total;
-        groups[1] = ng;
-        groups[2] = nv;
-    }
-}
-
 // A missing expert streamed by a gate/up launch: kFillGuBlocks blocks stream its rows (128 waves, each
 // with a row pair in flight per pass: 1 MiB for bf16 rows of 2048, 256 KiB for int4) and kFillSlices
 // blocks copy its down part.  Swept on both benchmark shapes (8-48 blocks, 16-64 pieces): 32 and 32 were
@@ -545,46 +462,40 @@ __device__ __forceinline__ void copy_down_parts(const FfnFill &fl, size_t expert
 }
 
 // -------------------------------------------------------------- gate/up ---
-// act[p, i] = w_p * silu(W_g[i] . x_t) * (W_u[i] . x_t) for every pair p of one
-// expert group.  One wave per row pair (gate row 2i, up row 2i+1): the pair's
-// weights are loaded once into registers and applied to each token of the
-// group.  ONE_TOKEN: T == 1, groups are the k ranks (+ shared), no table;
-// with plan.fill it also performs the step's fills (FfnFill): a missing
-// expert's rows come from the host store, plan.fill.blocks blocks stream them
-// (each wave a row pair per pass) and store them into the slot, and one more
-// row of blocks copies the blobs' down parts.
-template <int DT, int NCH, bool ONE_TOKEN, bool FULL>
+// One token: act[j, i] = w_j * silu(W_g[i] . x) * (W_u[i] . x) for its k ranks j (blockIdx.y; k is the
+// shared expert, weight 1).  One wave per row pair (gate row 2i, up row 2i+1).  With plan.fill it also
+// performs the step's fills (FfnFill): a missing expert's rows come from the host store, plan.fill.blocks
+// blocks stream them (each wave a row pair per pass) and store them into the slot, and one more row of
+// blocks copies the blobs' down parts.  (Several tokens: batch_ffn.hip.)
+template <int DT, int NCH, bool FULL>
 __global__ __launch_bounds__(kBlock) void gateup_kernel(
-    const float *__restrict__ x, int T, int H, int I, int E, int k, const int32_t *__restrict__ ids,
+    const float *__restrict__ x, int H, int I, int E, int k, const int32_t *__restrict__ ids,
     const int32_t *__restrict__ slot_of, const uint8_t *__restrict__ pool, size_t expert_bytes,
-    const uint8_t *__restrict__ shared_w, const float *__restrict__ weights, int *groups,
-    float *__restrict__ act, int *err, FfnPlan plan) {
+    const uint8_t *__restrict__ shared_w, const float *__restrict__ weights, float *__restrict__ act,
+    int *err, FfnPlan plan) {
     constexpr int EPC = Fmt<DT>::EPC;
-    // One token: the block stages x in LDS once instead of every wave reading it.  int4 (a wave streams
+    // The block stages x in LDS once instead of every wave reading it.  int4 (a wave streams
     // 2 KiB of weights but would read 8 KiB of x): as fp16 pairs with per-chunk scales (STAGE_X).  bf16:
     // as fp32, read chunk by chunk just before its products, which frees the registers that held the
     // wave's x (STAGE_XF; config 4's gate/up 10.5 -> 9.95 us).  f32 weights keep per-wave x.
-    constexpr bool STAGE_X = ONE_TOKEN && DT == INT4;
-    constexpr bool STAGE_XF = ONE_TOKEN && DT == BF16;
+    constexpr bool STAGE_X = DT == INT4;
+    constexpr bool STAGE_XF = DT == BF16;
     constexpr int NXF = (NCH * kWave * EPC / 4 + kBlock - 1) / kBlock;  // float4 of x per thread (STAGE_XF)
     const int lane = threadIdx.x & (kWave - 1);
     const int g = blockIdx.y;
     const uint8_t *blob;
     uint8_t *dst = nullptr;  // a missing expert streamed in by this launch: its rows are stored here too
     int istride = 0;         // then the wave's row pairs lie this far apart (0: one row pair per wave)
-    int pstart = 0, pcount = 1, single = 0;
-    const int *pairs = nullptr;
     unsigned long long *clk = nullptr;  // a filling launch: its blocks stamp the fill clock
     unsigned long long t_fill = 0;      // when this block began filling
     int i = blockIdx.x * (kBlock / kWave) + (threadIdx.x / kWave);
-    const int P = T * k;
-    // One token whose slots the device lookup wrote: every load that the blob's address depends on (the
+    // A token whose slots the device lookup wrote: every load that the blob's address depends on (the
     // rank's slot, the fill count, the fill list across the wave's lanes) is issued at once, and the token's
     // x after them, so that one wait covers the chain and x stays in flight into the weight stream.
     int s_ld = 0, nf_ld = 0, fslot = -1;
     long long fsrc = 0;
     bool dev_slot = false;
-    if constexpr (ONE_TOKEN) {
+    {
         clk = plan.fill.n ? plan.fill.clk : nullptr;
         if (plan.fill.n && g == int(gridDim.y) - 1) {
             const bool busy = int(blockIdx.x) < min(plan.fill.n[0], MOE_MAX_TOPK) * plan.fill.slices;
@@ -593,7 +504,6 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
             if (t0) devres::clk_record_fill(clk, t0, devres::clk_now());
             return;
         }
-        single = g;  // pair index: rank g, or T*k + 0 = k for the shared expert
         dev_slot = g < k && !plan.n;
         if (dev_slot) {
             // (the block-uniform words go through vector loads: earlier kernels on the stream wrote them)
@@ -606,8 +516,6 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
             }
             s_ld = load_stream_word((plan.rank_slot ? plan.rank_slot : ids) + g);
         }
-    } else {
-        if (g >= groups[0]) return;
     }
     if (!STAGE_X && !STAGE_XF && i >= I) return;  // when x is staged, every wave joins the block's staging below
     float xv[STAGE_X || STAGE_XF ? 1 : NCH][EPC];
@@ -615,28 +523,22 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
     uint4 xq[STAGE_X ? NCH : 1][4];       // staged int4 path: the chunk's activations as fp16 pairs
     float xbias[NCH];                     // ... the chunk's bias term
     int xsh_[NCH];                        // ... and its exponent shift
-    float wp0 = 1.f;  // combine weight of the first pair (1 for the shared expert)
-    if constexpr (!ONE_TOKEN) {
-        pstart = group_start(groups, T, k)[g];
-        pairs = group_pairs(groups, T, k);
-    }
+    float wp = 1.f;  // combine weight (1 for the shared expert)
     if constexpr (STAGE_XF) {
-        const float4 *xt4 = reinterpret_cast<const float4 *>(x);  // (one token)
-        wp0 = single < P ? weights[single] : 1.f;
+        const float4 *xt4 = reinterpret_cast<const float4 *>(x);
+        wp = g < k ? weights[g] : 1.f;
 #pragma unroll
         for (int r = 0; r < NXF; ++r) xf[r] = load_f4(xt4 + min(r * kBlock + int(threadIdx.x), H / 4 - 1));
     }
     if constexpr (!STAGE_X && !STAGE_XF) {
-        // The first pair's activations are loaded before the weight stream: loads
-        // retire in issue order, so waiting for x never waits for the weights.
-        const int p0 = ONE_TOKEN ? single : pairs[pstart];
-        wp0 = p0 < P ? weights[p0] : 1.f;
-        const float *xt = x + size_t(p0 < P ? p0 / k : p0 - P) * H;
+        // The activations are loaded before the weight stream: loads retire in
+        // issue order, so waiting for x never waits for the weights.
+        wp = g < k ? weights[g] : 1.f;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             const int col0 = (c * kWave + lane) * EPC;
             if ((FULL || col0 < H)) {
-                load_x<DT>(xt, col0, xv[c]);
+                load_x<DT>(x, col0, xv[c]);
             } else {
 #pragma unroll
                 for (int q = 0; q < EPC; ++q) xv[c][q] = 0.f;
@@ -647,7 +549,7 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
     // stream, so that packing it waits only for these loads.
     float4 xa[STAGE_X ? NCH : 1][2];
     if constexpr (STAGE_X) {
-        const float4 *xt4 = reinterpret_cast<const float4 *>(x + size_t(single < P ? single / k : single - P) * H);
+        const float4 *xt4 = reinterpret_cast<const float4 *>(x);
 #pragma unroll
         for (int r = 0; r < NCH; ++r) {
             const int f = r * kBlock + threadIdx.x;
@@ -656,7 +558,7 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
             xa[r][1] = in ? xt4[2 * f + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
-    if constexpr (ONE_TOKEN) {
+    {
         // (the loaded values pass through an empty asm after the x loads, so that no use of them -- and no
         // wait for them -- is scheduled before x is in flight)
         if (dev_slot) asm volatile("" : "+v"(s_ld), "+v"(nf_ld), "+v"(fslot), "+v"(fsrc)::"memory");
@@ -704,10 +606,6 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
         } else {
             blob = shared_w;
         }
-    } else {
-        const int s = group_slot(groups, T, k)[g];
-        pcount = group_count(groups, T, k)[g];
-        blob = s == -2 ? shared_w : pool + size_t(s) * expert_bytes;
     }
     const size_t rb = row_bytes_of(DT, H);
     for (bool first = true;; first = false) {
@@ -748,7 +646,7 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
         // follow.
         extern __shared__ uint4 xsh[];
         int2 *xaux = reinterpret_cast<int2 *>(xsh + NCH * 4 * kWave);
-        wp0 = single < P ? weights[single] : 1.f;
+        wp = g < k ? weights[g] : 1.f;
         // x passes through an empty asm after the weight loads: otherwise the compiler hoists the staging's
         // first steps above the loop, and their wait for x holds the weight loads back
 #pragma unroll
@@ -802,16 +700,7 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
             }
         }
     }
-    for (int q = 0; q < pcount; ++q) {
-        const int p = ONE_TOKEN ? single : pairs[pstart + q];
-        if (!STAGE_X && !STAGE_XF && q > 0) {  // (a staged token is one pair)
-            const float *xt = x + size_t(p < P ? p / k : p - P) * H;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int col0 = (c * kWave + lane) * EPC;
-                if ((FULL || col0 < H)) load_x<DT>(xt, col0, xv[STAGE_X || STAGE_XF ? 0 : c]);
-            }
-        }
+    {
         float ga = 0.f, ua = 0.f;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -846,9 +735,8 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
         }
         ga = wave_sum(ga);
         ua = wave_sum(ua);
-        // the pair's combine weight is folded in here
-        const float wp = q == 0 ? wp0 : (p < P ? weights[p] : 1.f);
-        if (lane == 0) act[size_t(p) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
+        // the combine weight is folded in here
+        if (lane == 0) act[size_t(g) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
     }
     if (!istride) break;  // block-uniform; no barrier follows the first pass
     i += istride;
@@ -1283,17 +1171,17 @@ size_t down_offset(int H, int I, int dtype) {
 
 static size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 
+// The activations, and room that no kernel uses now (a table of the pairs once): the size is part of the ABI,
+// which calls the fixed scratch accepts depends on it.
 size_t ffn_workspace_bytes(int T, int k, int I) {
     const size_t act = align256(sizeof(float) * size_t(T * k + T) * I);
     const size_t grp = align256(sizeof(int) * size_t(4 + 3 * (T * k + 1) + T * k + T));
     return act + grp;
 }
 
-FfnWorkspace ffn_workspace(void *base, int T, int k, int I) {
+FfnWorkspace ffn_workspace(void *base, int, int, int) {
     FfnWorkspace w;
     w.act = static_cast<float *>(base);
-    w.groups = reinterpret_cast<int *>(static_cast<char *>(base) +
-                                       align256(sizeof(float) * size_t(T * k + T) * I));
     return w;
 }
 
@@ -1417,13 +1305,7 @@ hipError_t launch_expert_ffn(const float *x, int T, int H, int I, int E, int k, 
     const int has_shared = shared_w != nullptr;
     const auto *pl = static_cast<const uint8_t *>(pool);
     const auto *sw = static_cast<const uint8_t *>(shared_w);
-    if (!one && (parts & kFfnGateUp)) {
-        group_pairs_kernel<<<1, kBlock, 0, s>>>(ids, T, k, E, slot_of, has_shared, ws.groups, err_flags);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const int groups = one ? k + has_shared : (T * k < E ? T * k : E) + has_shared;
-    const dim3 ggrid((I + 3) / 4, groups + (pl1.fill.n ? 1 : 0));  // + the blocks copying down parts
+    const dim3 ggrid((I + 3) / 4, k + has_shared + (pl1.fill.n ? 1 : 0));  // + the blocks copying down parts
     const int nch = chunks_per_row(H, dtype);
     // One-token int4 x staging covers every lane's chunk slot: [nch][4][64] words of fp16 pairs, then an
     // (exponent shift, bias term) pair per slot.
@@ -1446,16 +1328,18 @@ hipError_t launch_expert_ffn(const float *x, int T, int H, int I, int E, int k, 
     // FULL: every lane's chunk slots lie inside the row (H = nch * 64 * elements per chunk), no bound checks
     const bool full = H == nch * kWave * elems_per_chunk(dtype);
 #define GU_LAUNCH(DT, N, F)                                                                         \
-    (one ? launch(gateup_kernel<DT, N, true, F>, ggrid, kBlock, x_lds, s, x, T, H, I, E, k, ids,    \
-                  slot_of, pl, expert_bytes, sw, weights, ws.groups, ws.act, err_flags, pl1)        \
-         : launch(gateup_kernel<DT, N, false, F>, ggrid, kBlock, 0, s, x, T, H, I, E, k, ids,       \
-                  slot_of, pl, expert_bytes, sw, weights, ws.groups, ws.act, err_flags, FfnPlan{}))
+    launch(gateup_kernel<DT, N, F>, ggrid, kBlock, x_lds, s, x, H, I, E, k, ids, slot_of, pl, expert_bytes, \
+           sw, weights, ws.act, err_flags, pl1)
 #define GU_CASE(DT, N)                                                                              \
     if (!launched && dtype == DT && nch == N) {                                                     \
         e = full ? GU_LAUNCH(DT, N, true) : GU_LAUNCH(DT, N, false);                                \
         launched = true;                                                                            \
     }
     hipError_t e = hipSuccess;
+    if (!launched && !one) {  // 2 to 16 tokens: on the matrix cores
+        e = launch_batch_gateup(x, T, H, I, E, k, ids, weights, slot_of, pl, expert_bytes, dtype, sw, ws.act, err_flags, s);
+        launched = true;
+    }
     GU_CASE(F32, 1) GU_CASE(F32, 2) GU_CASE(F32, 4) GU_CASE(F32, 8)
     GU_CASE(BF16, 1) GU_CASE(BF16, 2) GU_CASE(BF16, 4) GU_CASE(BF16, 8)
     GU_CASE(INT4, 1) GU_CASE(INT4, 2) GU_CASE(INT4, 4) GU_CASE(INT4, 8)

@@ -215,6 +215,29 @@ def test_ffn_groups_of_many_tokens(dtype):
         check_ffn(wl, x, ids, w, ex, sh, slot_perm=rng.permutation(wl.E))
 
 
+@pytest.mark.parametrize("dtype,H", [(synth.F32, 128), (synth.F32, 1152), (synth.F32, 2048), (synth.BF16, 128),
+                                     (synth.BF16, 1024), (synth.BF16, 1152), (synth.BF16, 2176), (synth.BF16, 4096),
+                                     (synth.INT4G128, 128), (synth.INT4G128, 1024), (synth.INT4G128, 1152),
+                                     (synth.INT4G128, 2176)])
+def test_ffn_batch_widths(dtype, H):
+    """Several tokens at widths on each side of what a wave holds at once (idle waves, a ragged last share, more
+    than one pass), two and sixteen tokens, an expert named by more than 16 (token, rank) pairs, a call of the
+    fewest items.  Sums of at most 4096 fp32 terms: 1e-5 normwise for fp32 and bf16 weights; the int4 down
+    projection takes fp16 activations (2^-11 per term): 1e-3."""
+    wl = synth.Workload("batch widths", H=H, E=9, k=5, I=128, dtype=dtype, router_dtype=synth.F32, shared=True,
+                        cfg_id=300 + H + dtype)
+    ex, sh = _experts(wl)
+    rng = np.random.default_rng(H + dtype)
+    for T in (2, 16):
+        x = rng.standard_normal((T, wl.H)).astype(np.float32)
+        ids = rng.integers(0, 3, (T, wl.k)).astype(np.int32)  # repeated within a token too: up to 30 pairs of one
+        ids[0, 0] = 8
+        w = rng.random((T, wl.k)).astype(np.float32)
+        bound = 1e-3 if dtype == synth.INT4G128 else 1e-5
+        assert check_ffn(wl, x, ids, w, ex, sh, slot_perm=rng.permutation(wl.E)) <= bound
+        assert check_ffn(wl, x, ids[:, :1], w[:, :1], ex, None) <= bound
+
+
 @pytest.mark.parametrize("dtype,H", [(synth.F32, 384), (synth.BF16, 256), (synth.BF16, 640), (synth.BF16, 3968),
                                      (synth.BF16, 4096), (synth.INT4G128, 256), (synth.INT4G128, 2176),
                                      (synth.INT4G128, 4224)])
