@@ -870,7 +870,13 @@ __global__ __launch_bounds__(BT) void down_combine_lds_kernel(
     constexpr int RH = (NS * 256 + BT - 1) / BT;
     constexpr int SM = HALF ? 2 * RH : (NS * EPC * kWave + 4 * BT - 1) / (4 * BT);
     extern __shared__ float4 aw4[];
-    const int t = blockIdx.y;
+    // Workgroup b runs on XCD b mod 8.  Consecutive row tiles go to the same XCD, so the blocks that share a
+    // cache line of int4 row scales share one L2; and a tile's tokens run there one after the other, so that
+    // the rows of an expert that several tokens chose come from HBM once (16 tokens of bf16 experts, H 2048, I 512,
+    // 302 MB of rows of which 122 MB distinct: 40 -> 30 us).
+    const unsigned nb = gridDim.x, b = blockIdx.y * nb + blockIdx.x, T_ = gridDim.y;
+    const int t = int((nb & 7) ? b % T_ : (b >> 3) % T_);
+    const int tile = int((nb & 7) ? b / T_ : (b & 7) * (nb >> 3) + (b >> 3) / T_);
     const int NE = k + (shared_w != nullptr);
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     // 1. where the entries live, resolved by every wave for itself (lane j < NE: entry j) into its own LDS
@@ -935,10 +941,7 @@ __global__ __launch_bounds__(BT) void down_combine_lds_kernel(
         ent_tab[wid][lane] = off;
     }
     wave_lds_sync();
-    // 3. weight loads of this wave's R output rows.  Workgroup b runs on XCD b mod 8: consecutive row tiles
-    // go to the same XCD, so the blocks that share a cache line of int4 row scales share one L2.
-    const int nb = gridDim.x;
-    const int tile = (nb & 7) ? int(blockIdx.x) : int(blockIdx.x & 7) * (nb >> 3) + int(blockIdx.x >> 3);
+    // 3. weight loads of this wave's R output rows.
     const int h0 = (tile * (BT / kWave) + (threadIdx.x / kWave)) * R;  // the wave's first row
     const size_t rb = row_bytes_of(DT, I);
     const unsigned cpr = unsigned(rb / 16);  // chunks per expert row
