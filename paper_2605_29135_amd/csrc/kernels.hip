@@ -1056,6 +1056,48 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(const float *__restrict
     y[idx] = accumulate ? y[idx] + acc : acc;
 }
 
+// The same sums, four consecutive outputs per thread (H a multiple of 4, 16-byte aligned pointers): every pair's
+// 16 bytes are loaded before the first is added, so a thread waits once per eight pairs.  2048 tokens of top-8 and
+// H 2048 (150 MB read): 42 -> 25 us, 6.0 TB/s.
+constexpr int kCombineAhead = 8;
+__global__ __launch_bounds__(kBlock) void combine4_kernel(const float4 *__restrict__ yp, const float *__restrict__ w,
+                                                          const float4 *__restrict__ ys, int T, int k, int H4,
+                                                          float4 *__restrict__ y, int accumulate) {
+    const size_t idx = size_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (idx >= size_t(T) * H4) return;
+    const size_t t = idx / H4, h = idx - t * H4;
+    const float4 *row = yp + t * k * H4 + h;
+    const float *wt = w + t * k;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j0 = 0; j0 < k; j0 += kCombineAhead) {
+        float4 v[kCombineAhead];
+        float wj[kCombineAhead];
+#pragma unroll
+        for (int u = 0; u < kCombineAhead; ++u) {
+            const int j = min(j0 + u, k - 1);
+            v[u] = load_f4(row + size_t(j) * H4);
+            wj[u] = wt[j];
+        }
+#pragma unroll
+        for (int u = 0; u < kCombineAhead; ++u) {
+            if (j0 + u >= k) break;
+            acc.x += wj[u] * v[u].x;
+            acc.y += wj[u] * v[u].y;
+            acc.z += wj[u] * v[u].z;
+            acc.w += wj[u] * v[u].w;
+        }
+    }
+    if (ys) {
+        const float4 s = ys[idx];
+        acc = make_float4(acc.x + s.x, acc.y + s.y, acc.z + s.z, acc.w + s.w);
+    }
+    if (accumulate) {
+        const float4 o = y[idx];
+        acc = make_float4(o.x + acc.x, o.y + acc.y, o.z + acc.z, o.w + acc.w);
+    }
+    y[idx] = acc;
+}
+
 // ------------------------------------------------------------ slot table ---
 // Expert fills as one kernel: each block streams a share of one expert blob
 // from pinned host memory (read over PCIe) into its HBM slot; block (0, 0) also
@@ -1379,6 +1421,14 @@ hipError_t launch_combine(const float *y_partial, const float *weights, const fl
                           int k, int H, float *y, bool accumulate, hipStream_t s) {
     const size_t n = size_t(T) * H;
     if (n == 0) return hipSuccess;
+    const uintptr_t ptrs = reinterpret_cast<uintptr_t>(y_partial) | reinterpret_cast<uintptr_t>(y_shared) |
+                           reinterpret_cast<uintptr_t>(y);
+    if (H % 4 == 0 && ptrs % 16 == 0) {
+        combine4_kernel<<<unsigned((n / 4 + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+            reinterpret_cast<const float4 *>(y_partial), weights, reinterpret_cast<const float4 *>(y_shared), T, k, H / 4,
+            reinterpret_cast<float4 *>(y), accumulate ? 1 : 0);
+        return hipGetLastError();
+    }
     combine_kernel<<<unsigned((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(y_partial, weights, y_shared, T,
                                                                           k, H, y, accumulate ? 1 : 0);
     return hipGetLastError();

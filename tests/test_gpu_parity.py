@@ -310,6 +310,21 @@ def test_combine_parity():
     assert normwise(base.cpu().numpy(), ref) <= 1e-6
 
 
+@pytest.mark.parametrize("T,k,H,shift", [(3, 8, 130, 0), (3, 9, 132, 0), (2, 17, 64, 0), (3, 8, 128, 1), (1, 1, 4, 0)])
+def test_combine_widths_and_alignment(T, k, H, shift):
+    """Widths that four outputs per thread do and do not divide, more ranks than are loaded ahead (8), and
+    buffers off 16-byte alignment: every form gives the sums in rank order.  Bound: k + 1 fp32 roundings."""
+    rng = np.random.default_rng(H + k)
+    yp = rng.standard_normal((T, k, H)).astype(np.float32)
+    w = rng.random((T, k)).astype(np.float32)
+    ys = rng.standard_normal((T, H)).astype(np.float32)
+    off = torch.empty(T * k * H + shift, dtype=torch.float32, device=DEV)[shift:].view(T, k, H)
+    off.copy_(dev(yp))
+    y = moe.moe_combine(off, dev(w), dev(ys))
+    ref = np.einsum("tk,tkh->th", w.astype(np.float64), yp.astype(np.float64)) + ys
+    assert normwise(y.cpu().numpy(), ref) <= 2e-7 * (k + 1)
+
+
 # ------------------------------------------------------- budgeted stack ---
 def _pinned_store(wl, layers_alias=False):
     L_store = 1 if layers_alias else wl.L
