@@ -31,6 +31,7 @@ constexpr int kTileM = 64;        // pair rows per tile
 constexpr int kWaveN = 64;        // output columns per wave
 constexpr int kTileN = 4 * kWaveN;  // output columns per block
 constexpr int kPlanThreads = 1024;
+constexpr int kPlanIds = 8;        // ids in flight per thread of the grouping block
 constexpr int kXcds = 8;          // gfx950 dispatches consecutive workgroups round-robin over 8 XCDs
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -105,15 +106,23 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
         slot[g] = g == E ? -2 : (slot_of ? slot_of[g] : g);
     }
     __syncthreads();
-    for (int p = tid; p < P; p += kPlanThreads) {
-        const int e = ids[p];
-        const bool in = e >= 0 && e < E;
-        if (!in || slot[e] < 0) {
-            atomicOr(err, in ? kErrNotResident : kErrRange);
-            for (int h = 0; h < H; ++h) ws.y_part[size_t(p) * H + h] = 0.f;
-            continue;
+    // eight ids per thread and pass, loaded together (one load latency per 8192 pairs, not per 1024)
+    for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
+        int e[kPlanIds];
+#pragma unroll
+        for (int u = 0; u < kPlanIds; ++u) e[u] = ids[min(p0 + u * kPlanThreads, P - 1)];
+#pragma unroll
+        for (int u = 0; u < kPlanIds; ++u) {
+            const int p = p0 + u * kPlanThreads;
+            if (p >= P) break;
+            const bool in = e[u] >= 0 && e[u] < E;
+            if (!in || slot[e[u]] < 0) {
+                atomicOr(err, in ? kErrNotResident : kErrRange);
+                for (int h = 0; h < H; ++h) ws.y_part[size_t(p) * H + h] = 0.f;
+                continue;
+            }
+            atomicAdd(&cnt[e[u]], 1);
         }
-        atomicAdd(&cnt[e], 1);
     }
     __syncthreads();
     if (tid == 0) cnt[E] = has_shared ? T : 0;
@@ -157,10 +166,17 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
             }
         }
     }
-    for (int p = tid; p < P; p += kPlanThreads) {
-        const int e = ids[p];
-        if (e < 0 || e >= E || slot[e] < 0) continue;
-        ws.sorted[off[e] + atomicAdd(&cur[e], 1)] = p;
+    for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
+        int e[kPlanIds];
+#pragma unroll
+        for (int u = 0; u < kPlanIds; ++u) e[u] = ids[min(p0 + u * kPlanThreads, P - 1)];
+#pragma unroll
+        for (int u = 0; u < kPlanIds; ++u) {
+            const int p = p0 + u * kPlanThreads;
+            if (p >= P) break;
+            if (e[u] < 0 || e[u] >= E || slot[e[u]] < 0) continue;
+            ws.sorted[off[e[u]] + atomicAdd(&cur[e[u]], 1)] = p;
+        }
     }
     if (has_shared)
         for (int t = tid; t < T; t += kPlanThreads) ws.sorted[off[E] + t] = P + t;
@@ -182,10 +198,187 @@ struct Round {
     static constexpr int B16 = DT == INT4 ? 1 : SEG / 8;  // 16-byte weight loads per lane and column block
 };
 
+// The int4 gate/up GEMM.  tmp = A (136 + Q)^T - 136 * S_m on the matrix cores (the accumulators start from -136
+// times the row's group sum), then acc += s_n * tmp.  Bound by the vector cache's address lookups, the latency of a
+// round's loads and the unpacking more than by the matrix cores: so A rows are staged by consecutive threads (a load
+// instruction touches 8 cache lines instead of 32), and the scales and group sums of 16 rounds are staged at once
+// instead of five small loads per round.  2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> 160 us.
+// Measured and not kept: weights two rounds ahead (spills: 227 us), 80- and 96-row tiles of 128 columns in two or
+// three blocks per compute unit (254-270 us), products and unpacking interleaved by scheduling groups (222 us), the
+// same staging in the down GEMM (112-135 against 103 us: its four rounds per block are mostly start-up) and, for bf16,
+// waves that split the reduction range without LDS (230 against 171 us: four times the activation traffic).
+constexpr int kMetaRounds = 16;  // rounds whose scales and group sums are staged together
+__global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int H, int I, int k,
+                                                                   const uint8_t *__restrict__ pool, size_t expert_bytes,
+                                                                   const uint8_t *__restrict__ shared_w, int nblk_n,
+                                                                   PrefillWorkspace ws) {
+    using R = Round<INT4>;
+    constexpr int LPR = R::BK / 8;              // threads per A row when staging: 16 bytes each
+    constexpr int RPI = kBlock / LPR, AI = kTileM / RPI;  // A rows per load of the block, loads per round
+    __shared__ __align__(16) uint16_t As[2][kTileM * R::LDS];
+    __shared__ __align__(16) float Ss[kMetaRounds][kTileM];  // -136 x group sums of the tile rows
+    __shared__ uint16_t Sc[kMetaRounds][kTileN];             // the columns' scales
+    __shared__ float Sred[4][kTileM];                        // epilogue: per-wave activation sums
+    __shared__ int arow[kTileM];                             // pair id of each tile row (-1 = padding)
+    // XCD-aware order, as below
+    const int nwork = ws.hdr[0] * nblk_n;
+    const int chunk = (nwork + kXcds - 1) / kXcds;
+    const int idx = blockIdx.x / kXcds;
+    if (idx >= chunk) return;
+    const int work = (blockIdx.x % kXcds) * chunk + idx;
+    if (work >= nwork) return;
+    const int tile = work / nblk_n, nb = work % nblk_n;
+
+    const int P = T * k;
+    const int g = ws.tile_g[tile];
+    const int base = ws.g_off[g] + ws.tile_r0[tile];
+    const int rows = min(kTileM, ws.g_off[g + 1] - base);
+    const int sl = ws.g_slot[g];
+    const uint8_t *bmat = sl == -2 ? shared_w : pool + size_t(sl) * expert_bytes;
+    const int N = 2 * I, KG = H / 128;  // KG: quantisation groups per row, one round each
+    const uint16_t *bscale = reinterpret_cast<const uint16_t *>(bmat + size_t(N) * H / 2);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lr = lane % 16, lg = lane / 16;
+    const int wn0 = nb * kTileN + wave * kWaveN;  // (N is a multiple of 256: every column is in range)
+
+    if (tid < kTileM) arow[tid] = tid < rows ? ws.sorted[base + tid] : -1;
+    __syncthreads();
+    auto token = [&](int r) {  // padding rows read row 0's token; not stored
+        const int p = arow[r < rows ? r : 0];
+        return size_t(p < P ? p / k : p - P);
+    };
+    const int sc = (tid % LPR) * 8;
+    const uint16_t *asrc[AI];
+#pragma unroll
+    for (int i = 0; i < AI; ++i) asrc[i] = ws.xb + token(i * RPI + tid / LPR) * H + sc;
+    // the scales and group sums of rounds [r0, r0 + kMetaRounds) into LDS, all loads in flight together
+    auto stage_meta = [&](int r0) {
+        const uint16_t *sn = bscale + size_t(nb * kTileN + tid) * KG;
+        const int row = tid % kTileM;
+        const float *ss = ws.sx + token(row) * KG;
+        uint16_t v[kMetaRounds];
+        float f[kMetaRounds / 4];
+#pragma unroll
+        for (int q = 0; q < kMetaRounds; ++q) v[q] = sn[min(r0 + q, KG - 1)];
+#pragma unroll
+        for (int q = 0; q < kMetaRounds / 4; ++q) f[q] = ss[min(r0 + 4 * q + tid / kTileM, KG - 1)];
+#pragma unroll
+        for (int q = 0; q < kMetaRounds; ++q) Sc[q][tid] = v[q];
+#pragma unroll
+        for (int q = 0; q < kMetaRounds / 4; ++q) Ss[4 * q + tid / kTileM][row] = -136.f * f[q];
+    };
+
+    auto body = [&](auto mb_tag) __attribute__((always_inline)) {
+        constexpr int MB = decltype(mb_tag)::value;
+        floatx4 acc[MB][4];
+    #pragma unroll
+        for (int i = 0; i < MB; ++i)
+    #pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        u32x4 ra[AI];  // next round's activations of this thread
+        uint4 rb[4];   // next round's weights of this lane, one entry per 16-column block
+        uint32_t boff[4];  // 32-bit byte offsets of this lane's weight rows within the expert matrix
+    #pragma unroll
+        for (int j = 0; j < 4; ++j) boff[j] = uint32_t(wn0 + 16 * j + lr) * uint32_t(H / 2) + uint32_t(R::SEG * lg / 2);
+        // Software pipeline: iteration r issues round r + 1's loads, multiplies round r out of LDS and registers, then
+        // stores round r + 1's A into the other LDS buffer.
+        for (int r = -1; r < KG; ++r) {
+            uint4 cb[4];
+    #pragma unroll
+            for (int j = 0; j < 4; ++j) cb[j] = rb[j];
+            if (r + 1 < KG) {
+                const int k0 = (r + 1) * R::BK;
+    #pragma unroll
+                for (int i = 0; i < AI; ++i) ra[i] = *reinterpret_cast<const u32x4 *>(asrc[i] + k0);
+    #pragma unroll
+                for (int j = 0; j < 4; ++j) rb[j] = *reinterpret_cast<const uint4 *>(bmat + boff[j] + uint32_t(k0 / 2));
+            }
+            if (r >= 0) {
+                const int buf = r & 1;
+                floatx4 tmp[MB][4];
+    #pragma unroll
+                for (int s = 0; s < R::STEPS; ++s) {
+                    bf16x8 a[MB];
+    #pragma unroll
+                    for (int i = 0; i < MB; ++i)
+                        a[i] = *reinterpret_cast<const bf16x8 *>(&As[buf][(16 * i + lr) * R::LDS + R::SEG * lg + 8 * s]);
+                    floatx4 s0[MB];  // rows of this lane: m = 16i + 4lg + q
+                    if (s == 0)
+    #pragma unroll
+                        for (int i = 0; i < MB; ++i)
+                            s0[i] = *reinterpret_cast<const floatx4 *>(&Ss[r % kMetaRounds][16 * i + 4 * lg]);
+    #pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t d = s == 0 ? cb[j].x : s == 1 ? cb[j].y : s == 2 ? cb[j].z : cb[j].w;
+                        const bf16x8 b = int4_offset8(d);
+    #pragma unroll
+                        for (int i = 0; i < MB; ++i)
+                            tmp[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, s == 0 ? s0[i] : tmp[i][j], 0, 0, 0);
+                    }
+                }
+    #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float cs = bf16_bits_to_float(Sc[r % kMetaRounds][wave * kWaveN + 16 * j + lr]);
+    #pragma unroll
+                    for (int i = 0; i < MB; ++i)
+    #pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[i][j][q] = fmaf(cs, tmp[i][j][q], acc[i][j][q]);
+                }
+            }
+            if (r + 1 < KG) {
+                if ((r + 1) % kMetaRounds == 0) {  // (block-uniform: the first round of 16)
+                    if (r >= 0) __syncthreads();
+                    stage_meta(r + 1);
+                }
+    #pragma unroll
+                for (int i = 0; i < AI; ++i)
+                    *reinterpret_cast<u32x4 *>(&As[(r + 1) & 1][(i * RPI + tid / LPR) * R::LDS + sc]) = ra[i];
+            }
+            __syncthreads();
+        }
+
+        // epilogue: lane holds C[m = 16i + 4*lg + q][n = wn0 + 16j + lr]; gate and up columns are neighbouring lanes.
+        // The rows' activation sums are the down GEMM's group sums: this block's 256 columns are the 128 activation
+        // columns of down group nb.
+    #pragma unroll
+        for (int i = 0; i < MB; ++i)
+    #pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float rowsum = 0.f;  // this lane's bf16 activations
+                const int m = 16 * i + 4 * lg + q;
+                const int p = arow[m];
+    #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float v = acc[i][j][q];
+                    const float partner = dpp<0xB1>(v);
+                    if ((lr & 1) == 0 && p >= 0) {
+                        const uint32_t ab = pack2(v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * partner, 0.f) & 0xffffu;
+                        const int c = (wn0 + 16 * j + lr) / 2;
+                        ws.act[size_t(base + m) * I + (c & ~7) + perm8_pos(c & 7)] = uint16_t(ab);
+                        rowsum += __uint_as_float(ab << 16);
+                    }
+                }
+                rowsum += __shfl_xor(rowsum, 1);
+                rowsum += __shfl_xor(rowsum, 2);
+                rowsum += __shfl_xor(rowsum, 4);
+                rowsum += __shfl_xor(rowsum, 8);
+                if (lr == 0) Sred[wave][m] = rowsum;
+            }
+        __syncthreads();
+        if (tid < rows) ws.sa[size_t(base + tid) * (I / 128) + nb] = Sred[0][tid] + Sred[1][tid] + Sred[2][tid] + Sred[3][tid];
+    };
+    switch ((rows + 15) / 16) {
+        case 1: body(std::integral_constant<int, 1>{}); break;
+        case 2: body(std::integral_constant<int, 2>{}); break;
+        case 3: body(std::integral_constant<int, 3>{}); break;
+        default: body(std::integral_constant<int, 4>{}); break;
+    }
+}
+
 // int4: per round, tmp = A (136 + Q)^T on the matrix cores, then
 //   acc += s_n * (tmp - 136 * S_m)
 // with s_n the column's scale and S_m the row's sum of A over the group (read
-// from ws.sx for x, ws.sa for the activations).  bf16: acc += A W^T directly.
+// from ws.sa).  bf16: acc += A W^T directly.  (int4 gate/up: prefill_gateup_i4_kernel.)
 template <int DT, bool DOWN>
 __global__ __launch_bounds__(kBlock, 2) void prefill_gemm_kernel(int T, int H, int I, int k,
                                                               const uint8_t *__restrict__ pool, size_t expert_bytes,
@@ -193,9 +386,9 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gemm_kernel(int T, int H, i
                                                               int nblk_n, PrefillWorkspace ws) {
     using R = Round<DT>;
     constexpr bool kOffset = DT == INT4;
+    static_assert(DOWN || !kOffset);
     __shared__ __align__(16) uint16_t As[2][kTileM * R::LDS];
     __shared__ __align__(16) float Ss[2][kTileM];  // int4: group sums of the tile rows
-    __shared__ float Sred[4][kTileM];              // int4 gate/up epilogue: per-wave activation sums
     __shared__ int arow[kTileM];                   // pair id of each tile row (-1 = padding)
     // XCD-aware order: the blocks of one tile (and neighbouring tiles of a group) share an XCD's L2
     const int nwork = ws.hdr[0] * nblk_n;
@@ -239,15 +432,7 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gemm_kernel(int T, int H, i
     }
     // group sums: thread tid < 64 stages row tid's sum of the next round
     const float *ssrc = nullptr;
-    if constexpr (kOffset) {
-        const int rr = tid < rows ? tid : 0;
-        if constexpr (DOWN) {
-            ssrc = ws.sa + size_t(base + rr) * KG;
-        } else {
-            const int p = arow[tid < kTileM ? rr : 0];
-            ssrc = ws.sx + size_t(p < P ? p / k : p - P) * KG;
-        }
-    }
+    if constexpr (kOffset) ssrc = ws.sa + size_t(base + (tid < rows ? tid : 0)) * KG;
 
     // The main loop and the epilogue are instantiated for 1..4 live 16-row blocks: 16-row blocks that
     // are all padding take no MFMA, A read or fold (a group of 70 rows has a second tile of 6 rows).
@@ -355,12 +540,10 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gemm_kernel(int T, int H, i
         }
 
         // epilogue: lane holds C[m = 16i + 4*lg + q][n = wn0 + 16j + lr]
-        float rowsum[MB][4];  // int4 gate/up: this lane's bf16 activations summed per row
     #pragma unroll
         for (int i = 0; i < MB; ++i)
     #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                rowsum[i][q] = 0.f;
                 const int m = 16 * i + 4 * lg + q;
                 const int p = arow[m];
     #pragma unroll
@@ -377,32 +560,11 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gemm_kernel(int T, int H, i
                         const float partner = dpp<0xB1>(v);
                         if ((lr & 1) == 0 && active && p >= 0) {
                             const float a = v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * partner;
-                            const uint32_t ab = pack2(a, 0.f) & 0xffffu;
-                            const int c = n / 2;
-                            const int pos = kOffset ? (c & ~7) + perm8_pos(c & 7) : c;
-                            ws.act[size_t(base + m) * I + pos] = uint16_t(ab);
-                            rowsum[i][q] += __uint_as_float(ab << 16);
+                            ws.act[size_t(base + m) * I + n / 2] = uint16_t(pack2(a, 0.f));
                         }
                     }
                 }
             }
-        if constexpr (kOffset && !DOWN) {
-            // group sums of the activations for the down GEMM: this block's 256 gate/up columns are
-            // the 128 activation columns of down group nb
-    #pragma unroll
-            for (int i = 0; i < MB; ++i)
-    #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v = rowsum[i][q];
-                    v += __shfl_xor(v, 1);
-                    v += __shfl_xor(v, 2);
-                    v += __shfl_xor(v, 4);
-                    v += __shfl_xor(v, 8);
-                    if (lr == 0) Sred[wave][16 * i + 4 * lg + q] = v;
-                }
-            __syncthreads();
-            if (tid < rows) ws.sa[size_t(base + tid) * (I / 128) + nb] = Sred[0][tid] + Sred[1][tid] + Sred[2][tid] + Sred[3][tid];
-        }
     };
     switch ((rows + 15) / 16) {
         case 1: body(std::integral_constant<int, 1>{}); break;
@@ -478,8 +640,7 @@ hipError_t launch_prefill_ffn(const float *x, int T, int H, int I, int E, int k,
     // grids rounded up to whole XCD rounds: the block -> work map needs 8 * ceil(work / 8) blocks
     const unsigned g1 = unsigned((mt * nb1 + kXcds - 1) / kXcds * kXcds), g2 = unsigned((mt * nb2 + kXcds - 1) / kXcds * kXcds);
     if (dtype == INT4) {
-        e = launch(prefill_gemm_kernel<INT4, false>, dim3(g1), dim3(kBlock), 0, s, T, H, I, k, pl,
-                   expert_bytes, sw, doff, nb1, ws);
+        e = launch(prefill_gateup_i4_kernel, dim3(g1), dim3(kBlock), 0, s, T, H, I, k, pl, expert_bytes, sw, nb1, ws);
         if (e == hipSuccess)
             e = launch(prefill_gemm_kernel<INT4, true>, dim3(g2), dim3(kBlock), 0, s, T, H, I, k, pl,
                        expert_bytes, sw, doff, nb2, ws);
