@@ -31,7 +31,8 @@ constexpr int kTileM = 64;        // pair rows per tile
 constexpr int kWaveN = 64;        // output columns per wave
 constexpr int kTileN = 4 * kWaveN;  // output columns per block
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanIds = 8;        // ids in flight per thread of the grouping block
+constexpr int kPlanKeep = 16;      // ids that a thread of the grouping block keeps in registers
+constexpr int kPlanIds = 8;        // ... or loads together, where there are more pairs
 constexpr int kXcds = 8;          // gfx950 dispatches consecutive workgroups round-robin over 8 XCDs
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -106,53 +107,79 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
         slot[g] = g == E ? -2 : (slot_of ? slot_of[g] : g);
     }
     __syncthreads();
-    // eight ids per thread and pass, loaded together (one load latency per 8192 pairs, not per 1024)
-    for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
-        int e[kPlanIds];
+    // A pair's expert (or -1): a bad id or an absent slot raises the flag and zeroes the pair's output row.
+    auto checked = [&](int e, int p) {
+        if (e >= 0 && e < E && slot[e] >= 0) return e;
+        atomicOr(err, e >= 0 && e < E ? kErrNotResident : kErrRange);
+        for (int h = 0; h < H; ++h) ws.y_part[size_t(p) * H + h] = 0.f;
+        return -1;
+    };
+    // Up to 16384 pairs: a thread's 16 ids are loaded together and stay in registers with their ranks within their
+    // experts' groups (one load latency and one pass of LDS atomics, where a load per 1024 pairs and two passes took
+    // 25 us for 2048 tokens of top-8).  More pairs: two passes, eight ids loaded together.
+    const bool kept = P <= kPlanKeep * kPlanThreads;
+    int ke[kPlanKeep], kr[kPlanKeep];
+    if (kept) {
 #pragma unroll
-        for (int u = 0; u < kPlanIds; ++u) e[u] = ids[min(p0 + u * kPlanThreads, P - 1)];
+        for (int u = 0; u < kPlanKeep; ++u) ke[u] = ids[min(tid + u * kPlanThreads, P - 1)];
 #pragma unroll
-        for (int u = 0; u < kPlanIds; ++u) {
-            const int p = p0 + u * kPlanThreads;
-            if (p >= P) break;
-            const bool in = e[u] >= 0 && e[u] < E;
-            if (!in || slot[e[u]] < 0) {
-                atomicOr(err, in ? kErrNotResident : kErrRange);
-                for (int h = 0; h < H; ++h) ws.y_part[size_t(p) * H + h] = 0.f;
-                continue;
+        for (int u = 0; u < kPlanKeep; ++u) {
+            const int p = tid + u * kPlanThreads;
+            ke[u] = p < P ? checked(ke[u], p) : -1;
+            if (ke[u] >= 0) kr[u] = atomicAdd(&cnt[ke[u]], 1);
+        }
+    } else {
+        for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
+            int e[kPlanIds];
+#pragma unroll
+            for (int u = 0; u < kPlanIds; ++u) e[u] = ids[min(p0 + u * kPlanThreads, P - 1)];
+#pragma unroll
+            for (int u = 0; u < kPlanIds; ++u) {
+                const int p = p0 + u * kPlanThreads;
+                if (p < P) e[u] = checked(e[u], p);
+                if (p < P && e[u] >= 0) atomicAdd(&cnt[e[u]], 1);
             }
-            atomicAdd(&cnt[e[u]], 1);
         }
     }
     __syncthreads();
     if (tid == 0) cnt[E] = has_shared ? T : 0;
     __syncthreads();
-    // exclusive scans of the group sizes and of their tile counts, by wave 0 in chunks of 64
-    if (tid < kWave) {
-        int carry = 0, tcarry = 0;
-        for (int g0 = 0; g0 < G; g0 += kWave) {
-            const int g = g0 + tid;
-            const int c = g < G ? cnt[g] : 0;
-            int v = c, tv = (c + kTileM - 1) / kTileM;
-            const int c_t = tv;
-            for (int d = 1; d < kWave; d <<= 1) {
-                const int y = __shfl_up(v, d), ty = __shfl_up(tv, d);
-                if (tid >= d) {
-                    v += y;
-                    tv += ty;
-                }
+    // exclusive scans of the group sizes and of their tile counts: 64 groups per wave, then the waves' totals
+    __shared__ int wsum[(MOE_MAX_EXPERTS + kWave) / kWave], wtiles[(MOE_MAX_EXPERTS + kWave) / kWave];
+    int sc_v = 0, sc_t = 0, sc_c = 0, sc_ct = 0;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    if (wave * kWave < G) {
+        sc_c = tid < G ? cnt[tid] : 0;
+        sc_ct = (sc_c + kTileM - 1) / kTileM;
+        sc_v = sc_c;
+        sc_t = sc_ct;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int y = __shfl_up(sc_v, d), ty = __shfl_up(sc_t, d);
+            if (lane >= d) {
+                sc_v += y;
+                sc_t += ty;
             }
-            if (g < G) {
-                off[g] = carry + v - c;
-                toff[g] = tcarry + tv - c_t;
-            }
-            carry += __shfl(v, kWave - 1);
-            tcarry += __shfl(tv, kWave - 1);
         }
-        if (tid == 0) {
-            off[G] = carry;
-            toff[G] = tcarry;
-            ws.hdr[0] = tcarry;
+        if (lane == kWave - 1) {
+            wsum[wave] = sc_v;
+            wtiles[wave] = sc_t;
+        }
+    }
+    __syncthreads();
+    if (wave * kWave < G) {
+        int before = 0, tbefore = 0;
+        for (int w = 0; w < wave; ++w) {
+            before += wsum[w];
+            tbefore += wtiles[w];
+        }
+        if (tid < G) {
+            off[tid] = before + sc_v - sc_c;
+            toff[tid] = tbefore + sc_t - sc_ct;
+        }
+        if (tid == G - 1) {
+            off[G] = before + sc_v;
+            toff[G] = tbefore + sc_t;
+            ws.hdr[0] = tbefore + sc_t;
         }
     }
     __syncthreads();
@@ -166,16 +193,21 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
             }
         }
     }
-    for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
-        int e[kPlanIds];
+    if (kept) {
 #pragma unroll
-        for (int u = 0; u < kPlanIds; ++u) e[u] = ids[min(p0 + u * kPlanThreads, P - 1)];
+        for (int u = 0; u < kPlanKeep; ++u)
+            if (ke[u] >= 0) ws.sorted[off[ke[u]] + kr[u]] = tid + u * kPlanThreads;
+    } else {
+        for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
+            int e[kPlanIds];
 #pragma unroll
-        for (int u = 0; u < kPlanIds; ++u) {
-            const int p = p0 + u * kPlanThreads;
-            if (p >= P) break;
-            if (e[u] < 0 || e[u] >= E || slot[e[u]] < 0) continue;
-            ws.sorted[off[e[u]] + atomicAdd(&cur[e[u]], 1)] = p;
+            for (int u = 0; u < kPlanIds; ++u) e[u] = ids[min(p0 + u * kPlanThreads, P - 1)];
+#pragma unroll
+            for (int u = 0; u < kPlanIds; ++u) {
+                const int p = p0 + u * kPlanThreads;
+                if (p >= P || e[u] < 0 || e[u] >= E || slot[e[u]] < 0) continue;
+                ws.sorted[off[e[u]] + atomicAdd(&cur[e[u]], 1)] = p;
+            }
         }
     }
     if (has_shared)

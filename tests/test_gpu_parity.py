@@ -914,6 +914,26 @@ def test_prefill_parity_small_ragged(dtype, shared):
         assert normwise(y, ref) <= PREFILL_TOL[dtype]
 
 
+@pytest.mark.parametrize("T,E,k,H,I,dtype,shared", [(16384, 130, 1, 128, 128, synth.BF16, False),
+                                                     (3000, 256, 6, 128, 128, synth.INT4G128, True),
+                                                     (21, 12, 3, 2176, 128, synth.INT4G128, True)])
+def test_prefill_plan_and_reduction_edges(T, E, k, H, I, dtype, shared):
+    """As many pairs as the grouping block keeps in registers (16384) and more (two passes), expert counts that
+    are no multiple of a wave and 256 + the shared one, and a reduction range of 17 rounds (scales and group sums
+    are staged 16 rounds at a time).  Sampled tokens against the oracle, the prefill tolerance."""
+    wl = synth.Workload("prefill-edges", H=H, E=E, k=k, I=I, dtype=dtype, router_dtype=synth.F32, shared=shared,
+                        cfg_id=500 + E + dtype)
+    ex, sh = _experts(wl)
+    rng = np.random.default_rng(T)
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    w = rng.random((T, k)).astype(np.float32)
+    y = run_prefill(wl, x, ids, w, ex, sh, slot_perm=rng.permutation(E))
+    pick = np.r_[0, T - 1, rng.integers(0, T, 200)]
+    ref = oracle.moe_ffn(x[pick], ids[pick], w[pick].astype(np.float64), ex, H, I, dtype, sh)
+    assert normwise(y[pick], ref) <= PREFILL_TOL[dtype]
+
+
 def test_prefill_config5_chunk():
     """Config 5's 2048-token chunk (E 256, top-8, int4-g128, shared expert) routed by its router."""
     wl = synth.workload(5, L=1)
