@@ -32,6 +32,7 @@ constexpr int kDownBlock = MOE_DOWN_BLOCK;
 constexpr int kDownSlots = 4; // 16-byte chunks per lane per pass of the down projection
 constexpr float kRmsEps = 1e-6f;
 constexpr int kRouterMfmaMinTokens = 16;  // from this many tokens on, bf16 routers run on the matrix cores
+constexpr size_t kRouterWide = 262144;    // ... and above this many logits in 32 x 64 tiles
 
 // ---------------------------------------------------------------- top-k ---
 // Order-preserving 32-bit key of a finite float (-0 ranks with +0).
@@ -324,106 +325,147 @@ __device__ __forceinline__ void split3(const float *v, rbf16x8 &t1, rbf16x8 &t2,
     t3 = __builtin_bit_cast(rbf16x8, make_uint4(c[0], c[1], c[2], c[3]));
 }
 
-constexpr int kRouterTileT = 16;   // tokens per block (one MFMA row block)
-constexpr int kRouterTileE = 32;   // experts per block (two 16-column MFMA blocks)
+// logits[t, e] = sum_i W[e, i] h[t, i] (+ bias[t, e]); W bf16 [E x H], H % 32 == 0; h = x, or with NORM
+// h = x / sqrt(mean(x^2) + eps), applied to the sums (a row's factor is known only when the row has been read).
+// A block takes 16 RG tokens x 16 CB experts; its 8 waves split the H range into contiguous slices of 32-wide k
+// steps, each wave issuing the loads of ROUND steps before its first product (lane (lr = l % 16, lg = l / 16)
+// supplies x[t0 + 16i + lr][k + 8lg .. +7] and W[e0 + 16j + lr][k + 8lg .. +7]), and the waves' partial tiles are
+// summed through LDS in wave order.  With NORM the blocks of a token row share the columns of h_out (may be NULL).
+// Few tokens take 16 x 32 tiles (more blocks); many take 32 x 64 ones, since the launch is then bound by what the
+// blocks read from L2: 2048 tokens x 256 experts, H 2048: 268 MB in 1024 blocks 38.8 us (and 7.0 us for a launch
+// that normalised the rows), 134 MB in 256 blocks 27 us with the norm.  At 262144 logits (512 narrow
+// blocks, one round of two per compute unit) narrow tiles are the faster ones (19 against 25 us), at 524288 wide
+// ones (27 against 33).
 constexpr int kRouterKWaves = 8;   // waves per block, each over its own slice of the H range
-constexpr int kRouterRound = 8;    // 32-wide k steps whose loads a wave issues together
-
-// h = x / sqrt(mean(x^2) + eps), one wave per token.
-__global__ __launch_bounds__(kBlock) void rmsnorm_rows_kernel(const float *__restrict__ x, int T, int H,
-                                                              float *__restrict__ h) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int t = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-    if (t >= T) return;
-    const float4 *xr = reinterpret_cast<const float4 *>(x + size_t(t) * H);
-    float ss = 0.f;
-    for (int c = lane; c < H / 4; c += kWave) {
-        const float4 v = xr[c];
-        ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
-    }
-    const float inv = rsqrtf(wave_sum(ss) / float(H) + kRmsEps);
-    float4 *hr = reinterpret_cast<float4 *>(h + size_t(t) * H);
-    for (int c = lane; c < H / 4; c += kWave) {
-        const float4 v = xr[c];
-        hr[c] = make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv);
-    }
-}
-
-// logits[t, e] = sum_i W[e, i] x[t, i] (+ bias[t, e]); W bf16 [E x H], H % 32 == 0.
-// A block takes 16 tokens x 32 experts; its 8 waves split the H range into
-// contiguous slices of 32-wide k steps, each wave issuing the loads of up to 8
-// steps before its first product (lane (lr = l % 16, lg = l / 16) supplies
-// x[t0 + lr][k + 8lg .. +7] and W[e0 + 16j + lr][k + 8lg .. +7]), and the
-// waves' partial tiles are summed through LDS in wave order.
+template <int RG, int CB, int ROUND, bool NORM>
 __global__ __launch_bounds__(kRouterKWaves * kWave) void router_mfma_kernel(const float *__restrict__ x,
                                                                            const uint16_t *__restrict__ w, int T,
                                                                            int H, int E,
                                                                            const float *__restrict__ bias,
-                                                                           float *__restrict__ logits) {
-    __shared__ float red[kRouterKWaves][2 * 4 * kWave];
+                                                                           float *__restrict__ logits,
+                                                                           float *__restrict__ h_out) {
+    constexpr int kThreads = kRouterKWaves * kWave;
+    __shared__ float red[kRouterKWaves][RG][2][4][kWave];  // two column blocks at a time
+    __shared__ float ssq[kRouterKWaves][16 * RG], inv_rms[16 * RG];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int lr = lane % 16, lg = lane / 16;
-    const int t0 = blockIdx.y * kRouterTileT, e0 = blockIdx.x * kRouterTileE;
-    const float *xr = x + size_t(min(t0 + lr, T - 1)) * H + 8 * lg;
-    const uint16_t *wr0 = w + size_t(min(e0 + lr, E - 1)) * H + 8 * lg;
-    const uint16_t *wr1 = w + size_t(min(e0 + 16 + lr, E - 1)) * H + 8 * lg;
+    const int t0 = blockIdx.y * 16 * RG, e0 = blockIdx.x * 16 * CB;
+    const float *xr[RG];
+    const uint16_t *wr[CB];
+#pragma unroll
+    for (int i = 0; i < RG; ++i) xr[i] = x + size_t(min(t0 + 16 * i + lr, T - 1)) * H + 8 * lg;
+#pragma unroll
+    for (int j = 0; j < CB; ++j) wr[j] = w + size_t(min(e0 + 16 * j + lr, E - 1)) * H + 8 * lg;
     const int nk = H / 32;                                     // k steps in all
     const int ns = (nk + kRouterKWaves - 1) / kRouterKWaves;   // steps per wave
     const int s_lo = wave * ns, s_hi = min(nk, s_lo + ns);     // this wave's steps (wave-uniform)
-    rfloatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-    static_assert(kRouterRound == 8, "the load fence below names eight steps");
-    for (int r0 = s_lo; r0 < s_hi; r0 += kRouterRound) {
-        u32x4 xa[kRouterRound], xb[kRouterRound], wa[kRouterRound], wb[kRouterRound];
+    rfloatx4 acc[RG][CB], low[RG][CB];  // the leading terms' products, the two smaller ones'
+    float ss[RG];
 #pragma unroll
-        for (int r = 0; r < kRouterRound; ++r) {  // every load issued (step clamped), products only for live steps
+    for (int i = 0; i < RG; ++i) {
+        ss[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < CB; ++j) acc[i][j] = low[i][j] = rfloatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int r0 = s_lo; r0 < s_hi; r0 += ROUND) {
+        u32x4 xv[ROUND][RG][2], wv[ROUND][CB];
+#pragma unroll
+        for (int r = 0; r < ROUND; ++r) {  // every load issued (step clamped), products only for live steps
             const int k = 32 * min(r0 + r, nk - 1);
-            xa[r] = *reinterpret_cast<const u32x4 *>(xr + k);
-            xb[r] = *reinterpret_cast<const u32x4 *>(xr + k + 4);
-            wa[r] = *reinterpret_cast<const u32x4 *>(wr0 + k);
-            wb[r] = *reinterpret_cast<const u32x4 *>(wr1 + k);
+#pragma unroll
+            for (int i = 0; i < RG; ++i) {
+                xv[r][i][0] = *reinterpret_cast<const u32x4 *>(xr[i] + k);
+                xv[r][i][1] = *reinterpret_cast<const u32x4 *>(xr[i] + k + 4);
+            }
+#pragma unroll
+            for (int j = 0; j < CB; ++j) wv[r][j] = *reinterpret_cast<const u32x4 *>(wr[j] + k);
         }
-        // One fence over every loaded register: the compiler cannot move a load past it, so the round's loads
+        // A fence over every loaded register: the compiler cannot move a load past it, so the round's loads
         // are in flight together and the wave waits once (left to itself it interleaves each step's loads with
         // the previous step's products, one load latency per step).
-#define RFENCE(r) "+v"(xa[r]), "+v"(xb[r]), "+v"(wa[r]), "+v"(wb[r])
-        asm volatile("" : RFENCE(0), RFENCE(1), RFENCE(2), RFENCE(3), RFENCE(4), RFENCE(5), RFENCE(6), RFENCE(7));
-#undef RFENCE
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int r = 0; r < kRouterRound; ++r) {
+        for (int r = 0; r < ROUND; ++r) {
             // a step past the wave's slice multiplies zero weights (no branch around the products)
             const bool live = r0 + r < s_hi;
-            const float v[8] = {__uint_as_float(xa[r].x), __uint_as_float(xa[r].y), __uint_as_float(xa[r].z),
-                                __uint_as_float(xa[r].w), __uint_as_float(xb[r].x), __uint_as_float(xb[r].y),
-                                __uint_as_float(xb[r].z), __uint_as_float(xb[r].w)};
-            const u32x4 z4 = {0u, 0u, 0u, 0u};
-            const rbf16x8 b0 = __builtin_bit_cast(rbf16x8, live ? wa[r] : z4);
-            const rbf16x8 b1 = __builtin_bit_cast(rbf16x8, live ? wb[r] : z4);
-            rbf16x8 a1, a2, a3;
-            split3(v, a1, a2, a3);
-            // smallest terms first
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3, b1, acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b1, acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc1, 0, 0, 0);
+            const uint32_t keep = live ? ~0u : 0u;
+            const u32x4 k4 = {keep, keep, keep, keep};
+#pragma unroll
+            for (int i = 0; i < RG; ++i) {
+                const u32x4 a = xv[r][i][0], b = xv[r][i][1];
+                const float v[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+                                    __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+                if constexpr (NORM) {
+                    float q = 0.f;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) q = fmaf(v[c], v[c], q);
+                    ss[i] += __uint_as_float(__float_as_uint(q) & keep);
+                }
+                rbf16x8 a1, a2, a3;
+                split3(v, a1, a2, a3);
+#pragma unroll
+                for (int j = 0; j < CB; ++j)
+                    low[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3, __builtin_bit_cast(rbf16x8, wv[r][j] & k4), low[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < CB; ++j)
+                    low[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, __builtin_bit_cast(rbf16x8, wv[r][j] & k4), low[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < CB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, __builtin_bit_cast(rbf16x8, wv[r][j] & k4), acc[i][j], 0, 0, 0);
+            }
         }
     }
-    // lane holds C[t = t0 + 4lg + q][e = e0 + 16j + lr] in acc_j[q]; entry (j, q, lane) of the tile is
-    // red[.][(j * 4 + q) * 64 + lane]
+    if constexpr (NORM) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        red[wave][q * kWave + lane] = acc0[q];
-        red[wave][(4 + q) * kWave + lane] = acc1[q];
+        for (int i = 0; i < RG; ++i) {
+            float q = ss[i];
+            q += __shfl_xor(q, 16);
+            q += __shfl_xor(q, 32);
+            if (lg == 0) ssq[wave][16 * i + lr] = q;
+        }
+        __syncthreads();
+        if (threadIdx.x < 16 * RG) {
+            float q = 0.f;
+#pragma unroll
+            for (int wv = 0; wv < kRouterKWaves; ++wv) q += ssq[wv][threadIdx.x];
+            inv_rms[threadIdx.x] = rsqrtf(q / float(H) + kRmsEps);
+        }  // (the barrier below stands before its first reader)
     }
-    __syncthreads();
-    const int i = threadIdx.x;  // one tile entry per thread: 8 x 64 entries, 512 threads
-    float v = 0.f;
+    // lane holds C[t = t0 + 16i + 4lg + q][e = e0 + 16j + lr] in acc[i][j][q]
 #pragma unroll
-    for (int wv = 0; wv < kRouterKWaves; ++wv) v += red[wv][i];
-    const int j = i / (4 * kWave), q = (i / kWave) % 4, l = i % kWave;
-    const int t = t0 + 4 * (l / 16) + q, e = e0 + 16 * j + l % 16;
-    if (t < T && e < E) logits[size_t(t) * E + e] = v + (bias ? bias[size_t(t) * E + e] : 0.f);
+    for (int h = 0; h < CB / 2; ++h) {
+        if (h) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < RG; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) red[wave][i][j][q][lane] = acc[i][2 * h + j][q] + low[i][2 * h + j][q];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {  // 512 entries per row group: one per thread
+            const int j = threadIdx.x / (4 * kWave), q = (threadIdx.x / kWave) % 4;
+            float v = 0.f;
+#pragma unroll
+            for (int wv = 0; wv < kRouterKWaves; ++wv) v += red[wv][i][j][q][lane];
+            const int tr = 16 * i + 4 * lg + q, t = t0 + tr, e = e0 + 16 * (2 * h + j) + lr;
+            if constexpr (NORM) v *= inv_rms[tr];
+            if (t < T && e < E) logits[size_t(t) * E + e] = v + (bias ? bias[size_t(t) * E + e] : 0.f);
+        }
+    }
+    if constexpr (NORM) {
+        if (h_out) {  // this block's share of the columns of its rows
+            const int c0 = H / 4 * blockIdx.x / gridDim.x, nc = H / 4 * (blockIdx.x + 1) / gridDim.x - c0;
+            for (int i = threadIdx.x; i < 16 * RG * nc; i += kThreads) {
+                const int tr = i / nc, c = c0 + i - tr * nc;
+                if (t0 + tr >= T) break;
+                const size_t at = size_t(t0 + tr) * (H / 4) + c;
+                const float4 v = reinterpret_cast<const float4 *>(x)[at];
+                const float f = inv_rms[tr];
+                reinterpret_cast<float4 *>(h_out)[at] = make_float4(v.x * f, v.y * f, v.z * f, v.w * f);
+            }
+        }
+    }
 }
 
 // A missing expert streamed by a gate/up launch: kFillGuBlocks blocks stream its rows (128 waves, each
@@ -1249,19 +1291,20 @@ hipError_t launch_router_logits(const float *x, const void *w, int w_dtype, int 
         if (bias == logits) return hipSuccess;
         return hipMemcpyAsync(logits, bias, sizeof(float) * size_t(T) * E, hipMemcpyDeviceToDevice, s);
     }
-    if (w_dtype == BF16 && T >= kRouterMfmaMinTokens && (!norm || h_out)) {
-        // many tokens: (pre-norm, then) the router product on the matrix cores
-        const float *src = x;
-        if (norm) {
-            rmsnorm_rows_kernel<<<(T + 3) / 4, kBlock, 0, s>>>(x, T, H, h_out);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            src = h_out;
-        }
-        const dim3 g((E + kRouterTileE - 1) / kRouterTileE, (T + kRouterTileT - 1) / kRouterTileT);
-        router_mfma_kernel<<<g, kRouterKWaves * kWave, 0, s>>>(src, static_cast<const uint16_t *>(w), T, H, E, bias,
-                                                               logits);
-        return hipGetLastError();
+    if (w_dtype == BF16 && T >= kRouterMfmaMinTokens && (!norm || h_out)) {  // many tokens: on the matrix cores
+        const auto *wb = static_cast<const uint16_t *>(w);
+#define ROUTER_MFMA(RG, CB, ROUND)                                                                                     \
+    {                                                                                                                  \
+        const dim3 g((E + 16 * CB - 1) / (16 * CB), (T + 16 * RG - 1) / (16 * RG));                                    \
+        if (norm)                                                                                                      \
+            router_mfma_kernel<RG, CB, ROUND, true><<<g, kRouterKWaves * kWave, 0, s>>>(x, wb, T, H, E, bias, logits, h_out); \
+        else                                                                                                           \
+            router_mfma_kernel<RG, CB, ROUND, false><<<g, kRouterKWaves * kWave, 0, s>>>(x, wb, T, H, E, bias, logits, nullptr); \
+        return hipGetLastError();                                                                                      \
+    }
+        if (size_t(T) * E > kRouterWide) ROUTER_MFMA(2, 4, 4)
+        ROUTER_MFMA(1, 2, 8)
+#undef ROUTER_MFMA
     }
     const dim3 grid((E + 3) / 4, T);
     const auto *wp = static_cast<const uint8_t *>(w);

@@ -102,6 +102,18 @@ def test_route_with_mask_bias_selects_the_drawn_sets():
         assert (np.sort(ids, axis=1) == sets[t, 0]).all()
 
 
+@pytest.mark.parametrize("T,E,H", [(2017, 130, 384), (2048, 128, 128), (2049, 128, 1152)])
+@pytest.mark.parametrize("norm", [False, True])
+def test_route_wide_tiles(T, E, H, norm):
+    """On each side of the number of logits from which the matrix-core router takes 32 x 64 tiles (262144), with
+    ragged token and expert tiles, waves without a share of the reduction range, and a bias."""
+    rng = np.random.default_rng(T + E)
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    wr = torch.from_numpy((0.02 * rng.standard_normal((E, H))).astype(np.float32)).to(torch.bfloat16)
+    bias = rng.standard_normal((T, E)).astype(np.float32)
+    check_route(x, wr.view(torch.int16).numpy().view(np.uint16), synth.BF16, 4, bias=bias, norm=norm)
+
+
 @pytest.mark.parametrize("E,k", [(16, 16), (256, 1), (256, 16), (64, 3), (130, 5)])
 def test_route_ties_and_edge_k(E, k):
     rng = np.random.default_rng(E + k)
