@@ -143,15 +143,15 @@ def _dev(t, name: str, dtype=None):
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+    if dtype is not None and t.dtype is not dtype and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
         raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
     return t.data_ptr()
 
 
 def _stream(stream):
-    import torch
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:  # the current device's stream as the raw handle (no Stream object per call)
+        import torch
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
