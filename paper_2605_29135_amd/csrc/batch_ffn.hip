@@ -17,6 +17,9 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxPairs = MOE_MAX_DECODE_TOKENS * MOE_MAX_TOPK;  // (token, rank) pairs of a call
 
+constexpr int kRowsMaxTokens = 5;  // bf16 experts: up to this many tokens one wave per row pair is the faster way (H 2048,
+                                   // I 768, top-8 of 128: 2 tokens 28.0 against 31.5 us, 4 44.3 against 46.7, 6 60.3 against 59.6, 12 102.8 against 94.7)
+
 // High halves of two floats as a bf16 pair (lo's in the low half).
 __device__ __forceinline__ uint32_t high_halves(float lo, float hi) {
     return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
@@ -369,17 +372,17 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
     }
 }
 
-// fp32 experts: one wave per row pair (gate row 2i, up row 2i + 1), its weights loaded once and applied to each
-// token of the expert (fp32 matrix instructions measured no faster here, and their longer chains of roundings
+// fp32 experts, and bf16 ones of up to kRowsMaxTokens tokens: one wave per row pair (gate row 2i, up row 2i + 1),
+// its weights loaded once and applied to each token of the expert (fp32 matrix instructions measured no faster here, and their longer chains of roundings
 // less exact).  Block (row pairs, p): for all the pairs of pair p's expert if p is the first of them (the
 // other blocks leave: each wave finds the expert's pairs by ballots over the ids, so that no launch groups
 // them first: 5.3 us of the 31.8 us of 7 tokens at H 1408, I 384); p = T * k is the shared expert.
-template <int NCH, bool FULL>
-__global__ __launch_bounds__(kBlock) void batch_gateup_f32_kernel(
+template <int DT, int NCH, bool FULL>
+__global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
     const float *__restrict__ x, int T, int H, int I, int E, int k, const int32_t *__restrict__ ids,
     const int32_t *__restrict__ slot_of, const uint8_t *__restrict__ pool, size_t expert_bytes,
     const uint8_t *__restrict__ shared_w, const float *__restrict__ weights, float *__restrict__ act, int *err) {
-    constexpr int EPC = Fmt<F32>::EPC;
+    constexpr int EPC = Fmt<DT>::EPC;
     __shared__ int members[kBlock / kWave][kMaxPairs];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int g = blockIdx.y, P = T * k;
@@ -425,7 +428,7 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_f32_kernel(
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     const int i = blockIdx.x * (kBlock / kWave) + wave;
     if (i >= I) return;
-    const size_t rb = row_bytes_of(F32, H);
+    const size_t rb = row_bytes_of(DT, H);
     const uint8_t *gate = blob + size_t(2 * i) * rb + 16 * lane;
     float xv[NCH][EPC];
     auto load_token = [&](int p) {
@@ -434,7 +437,7 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_f32_kernel(
         for (int c = 0; c < NCH; ++c) {
             const int col0 = (c * kWave + lane) * EPC;
             if (FULL || col0 < H) {
-                load_x<F32>(xt, col0, xv[c]);
+                load_x<DT>(xt, col0, xv[c]);
             } else {
 #pragma unroll
                 for (int q = 0; q < EPC; ++q) xv[c][q] = 0.f;
@@ -456,8 +459,8 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_f32_kernel(
         float ga = 0.f, ua = 0.f;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            ga += chunk_dot<F32>(wg[c], xv[c]);
-            ua += chunk_dot<F32>(wu[c], xv[c]);
+            ga += chunk_dot<DT>(wg[c], xv[c]);
+            ua += chunk_dot<DT>(wu[c], xv[c]);
         }
         ga = wave_sum(ga);
         ua = wave_sum(ua);
@@ -477,6 +480,20 @@ hipError_t launch_batch_gateup(const float *x, int T, int H, int I, int E, int k
                                                                        expert_bytes, shared_w, weights, act, err); \
         return hipGetLastError();                                                                              \
     }
+    if (dtype == F32 || (dtype == BF16 && T <= kRowsMaxTokens)) {
+        const dim3 grid(unsigned((I + kBlock / kWave - 1) / (kBlock / kWave)), unsigned(T * k + (shared_w ? 1 : 0)));
+        // FULL: every lane's chunk slots lie inside the row, no bound checks
+#define ROWS_CASE(DT, N)                                                                                             \
+    if (dtype == DT && H <= N * kWave * Fmt<DT>::EPC) {                                                              \
+        auto *kernel = H == N * kWave * Fmt<DT>::EPC ? batch_gateup_rows_kernel<DT, N, true> : batch_gateup_rows_kernel<DT, N, false>; \
+        kernel<<<grid, kBlock, 0, s>>>(x, T, H, I, E, k, ids, slot_of, pool, expert_bytes, shared_w, weights, act, err); \
+        return hipGetLastError();                                                                                    \
+    }
+        ROWS_CASE(F32, 1) ROWS_CASE(F32, 2) ROWS_CASE(F32, 4) ROWS_CASE(F32, 8)
+        ROWS_CASE(BF16, 1) ROWS_CASE(BF16, 2) ROWS_CASE(BF16, 4) ROWS_CASE(BF16, 8)
+#undef ROWS_CASE
+        return hipErrorInvalidValue;
+    }
     // the fewest steps per wave that hold a wave's share of the reduction range (longer ranges take passes)
 #define GU_CASE(DT)                                                                       \
     if (dtype == DT) {                                                                    \
@@ -488,17 +505,6 @@ hipError_t launch_batch_gateup(const float *x, int T, int H, int I, int E, int k
     GU_CASE(BF16) GU_CASE(INT4)
 #undef GU_CASE
 #undef GU_LAUNCH
-    if (dtype != F32) return hipErrorInvalidValue;
-    const dim3 grid(unsigned((I + kBlock / kWave - 1) / (kBlock / kWave)), unsigned(T * k + (shared_w ? 1 : 0)));
-    // FULL: every lane's chunk slots lie inside the row, no bound checks
-#define F32_CASE(N)                                                                                                  \
-    if (H <= N * kWave * Fmt<F32>::EPC) {                                                                            \
-        auto *kernel = H == N * kWave * Fmt<F32>::EPC ? batch_gateup_f32_kernel<N, true> : batch_gateup_f32_kernel<N, false>; \
-        kernel<<<grid, kBlock, 0, s>>>(x, T, H, I, E, k, ids, slot_of, pool, expert_bytes, shared_w, weights, act, err); \
-        return hipGetLastError();                                                                                    \
-    }
-    F32_CASE(1) F32_CASE(2) F32_CASE(4) F32_CASE(8)
-#undef F32_CASE
     return hipErrorInvalidValue;
 }
 

@@ -240,7 +240,7 @@ def test_ffn_batch_widths(dtype, H):
                         cfg_id=300 + H + dtype)
     ex, sh = _experts(wl)
     rng = np.random.default_rng(H + dtype)
-    for T in (2, 16):
+    for T in (2, 5, 6, 16):  # (bf16: up to 5 tokens one wave per row pair, above that the matrix cores)
         x = rng.standard_normal((T, wl.H)).astype(np.float32)
         ids = rng.integers(0, 3, (T, wl.k)).astype(np.int32)  # repeated within a token too: up to 30 pairs of one
         ids[0, 0] = 8
