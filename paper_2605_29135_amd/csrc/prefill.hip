@@ -234,7 +234,8 @@ struct Round {
 // times the row's group sum), then acc += s_n * tmp.  Bound by the vector cache's address lookups, the latency of a
 // round's loads and the unpacking more than by the matrix cores: so A rows are staged by consecutive threads (a load
 // instruction touches 8 cache lines instead of 32), and the scales and group sums of 16 rounds are staged at once
-// instead of five small loads per round.  2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> 160 us.
+// instead of five small loads per round; and each row's token is divided out once per row, not per thread and load.
+// 2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> about 155 us.
 // Measured and not kept: weights two rounds ahead (spills: 227 us), 80- and 96-row tiles of 128 columns in two or
 // three blocks per compute unit (254-270 us), products and unpacking interleaved by scheduling groups (222 us), the
 // same staging in the down GEMM (112-135 against 103 us: its four rounds per block are mostly start-up) and, for bf16,
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int
     __shared__ __align__(16) float Ss[kMetaRounds][kTileM];  // -136 x group sums of the tile rows
     __shared__ uint16_t Sc[kMetaRounds][kTileN];             // the columns' scales
     __shared__ float Sred[4][kTileM];                        // epilogue: per-wave activation sums
-    __shared__ int arow[kTileM];                             // pair id of each tile row (-1 = padding)
+    __shared__ int atok[kTileM];                             // token of each tile row (padding: row 0's)
     // XCD-aware order, as below
     const int nwork = ws.hdr[0] * nblk_n;
     const int chunk = (nwork + kXcds - 1) / kXcds;
@@ -273,31 +274,36 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int
     const int lr = lane % 16, lg = lane / 16;
     const int wn0 = nb * kTileN + wave * kWaveN;  // (N is a multiple of 256: every column is in range)
 
-    if (tid < kTileM) arow[tid] = tid < rows ? ws.sorted[base + tid] : -1;
+    if (tid < kTileM) {
+        const int p = ws.sorted[base + (tid < rows ? tid : 0)];
+        atok[tid] = p < P ? p / k : p - P;
+    }
     __syncthreads();
-    auto token = [&](int r) {  // padding rows read row 0's token; not stored
-        const int p = arow[r < rows ? r : 0];
-        return size_t(p < P ? p / k : p - P);
-    };
     const int sc = (tid % LPR) * 8;
     const uint16_t *asrc[AI];
 #pragma unroll
-    for (int i = 0; i < AI; ++i) asrc[i] = ws.xb + token(i * RPI + tid / LPR) * H + sc;
-    // the scales and group sums of rounds [r0, r0 + kMetaRounds) into LDS, all loads in flight together
-    auto stage_meta = [&](int r0) {
+    for (int i = 0; i < AI; ++i) asrc[i] = ws.xb + size_t(atok[i * RPI + tid / LPR]) * H + sc;
+    // the scales and group sums of rounds [r0, r0 + kMetaRounds) into LDS, all loads in flight together; of four
+    // rounds where no more are left (1500 tokens, H 512: the chunk 62.3 -> 60.9 us)
+    auto stage_rounds = [&](int r0, auto count) __attribute__((always_inline)) {
+        constexpr int NR = decltype(count)::value;
         const uint16_t *sn = bscale + size_t(nb * kTileN + tid) * KG;
         const int row = tid % kTileM;
-        const float *ss = ws.sx + token(row) * KG;
-        uint16_t v[kMetaRounds];
-        float f[kMetaRounds / 4];
+        const float *ss = ws.sx + size_t(atok[row]) * KG;
+        uint16_t v[NR];
+        float f[NR / 4];
 #pragma unroll
-        for (int q = 0; q < kMetaRounds; ++q) v[q] = sn[min(r0 + q, KG - 1)];
+        for (int q = 0; q < NR; ++q) v[q] = sn[min(r0 + q, KG - 1)];
 #pragma unroll
-        for (int q = 0; q < kMetaRounds / 4; ++q) f[q] = ss[min(r0 + 4 * q + tid / kTileM, KG - 1)];
+        for (int q = 0; q < NR / 4; ++q) f[q] = ss[min(r0 + 4 * q + tid / kTileM, KG - 1)];
 #pragma unroll
-        for (int q = 0; q < kMetaRounds; ++q) Sc[q][tid] = v[q];
+        for (int q = 0; q < NR; ++q) Sc[q][tid] = v[q];
 #pragma unroll
-        for (int q = 0; q < kMetaRounds / 4; ++q) Ss[4 * q + tid / kTileM][row] = -136.f * f[q];
+        for (int q = 0; q < NR / 4; ++q) Ss[4 * q + tid / kTileM][row] = -136.f * f[q];
+    };
+    auto stage_meta = [&](int r0) __attribute__((always_inline)) {
+        if (KG - r0 > 4) stage_rounds(r0, std::integral_constant<int, kMetaRounds>{});
+        else stage_rounds(r0, std::integral_constant<int, 4>{});
     };
 
     auto body = [&](auto mb_tag) __attribute__((always_inline)) {
@@ -378,12 +384,11 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int
             for (int q = 0; q < 4; ++q) {
                 float rowsum = 0.f;  // this lane's bf16 activations
                 const int m = 16 * i + 4 * lg + q;
-                const int p = arow[m];
     #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const float v = acc[i][j][q];
                     const float partner = dpp<0xB1>(v);
-                    if ((lr & 1) == 0 && p >= 0) {
+                    if ((lr & 1) == 0 && m < rows) {
                         const uint32_t ab = pack2(v * __builtin_amdgcn_rcpf(1.f + __expf(-v)) * partner, 0.f) & 0xffffu;
                         const int c = (wn0 + 16 * j + lr) / 2;
                         ws.act[size_t(base + m) * I + (c & ~7) + perm8_pos(c & 7)] = uint16_t(ab);
