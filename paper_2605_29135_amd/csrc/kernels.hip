@@ -325,6 +325,25 @@ __device__ __forceinline__ void split3(const float *v, rbf16x8 &t1, rbf16x8 &t2,
     t3 = __builtin_bit_cast(rbf16x8, make_uint4(c[0], c[1], c[2], c[3]));
 }
 
+// h = x / sqrt(mean(x^2) + eps), one wave per token (h may be x itself: a row is read before it is written).
+__global__ __launch_bounds__(kBlock) void rmsnorm_rows_kernel(const float *x, int T, int H, float *h) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int t = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    if (t >= T) return;
+    const float4 *xr = reinterpret_cast<const float4 *>(x + size_t(t) * H);
+    float ss = 0.f;
+    for (int c = lane; c < H / 4; c += kWave) {
+        const float4 v = xr[c];
+        ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
+    }
+    const float inv = rsqrtf(wave_sum(ss) / float(H) + kRmsEps);
+    float4 *hr = reinterpret_cast<float4 *>(h + size_t(t) * H);
+    for (int c = lane; c < H / 4; c += kWave) {
+        const float4 v = xr[c];
+        hr[c] = make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv);
+    }
+}
+
 // logits[t, e] = sum_i W[e, i] h[t, i] (+ bias[t, e]); W bf16 [E x H], H % 32 == 0; h = x, or with NORM
 // h = x / sqrt(mean(x^2) + eps), applied to the sums (a row's factor is known only when the row has been read).
 // A block takes 16 RG tokens x 16 CB experts; its 8 waves split the H range into contiguous slices of 32-wide k
@@ -1293,14 +1312,25 @@ hipError_t launch_router_logits(const float *x, const void *w, int w_dtype, int 
     }
     if (w_dtype == BF16 && T >= kRouterMfmaMinTokens && (!norm || h_out)) {  // many tokens: on the matrix cores
         const auto *wb = static_cast<const uint16_t *>(w);
+        // Normalised rows written over x (in place, or overlapping) would reach blocks that still read x: then the
+        // rows are normalised after the product.
+        const bool apart = !norm || h_out + size_t(T) * H <= x || x + size_t(T) * H <= h_out;
+        float *hw = apart ? h_out : nullptr;
+        const auto finish = [&]() {
+            if (apart) return hipGetLastError();
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            rmsnorm_rows_kernel<<<(T + 3) / 4, kBlock, 0, s>>>(x, T, H, h_out);
+            return hipGetLastError();
+        };
 #define ROUTER_MFMA(RG, CB, ROUND)                                                                                     \
     {                                                                                                                  \
         const dim3 g((E + 16 * CB - 1) / (16 * CB), (T + 16 * RG - 1) / (16 * RG));                                    \
         if (norm)                                                                                                      \
-            router_mfma_kernel<RG, CB, ROUND, true><<<g, kRouterKWaves * kWave, 0, s>>>(x, wb, T, H, E, bias, logits, h_out); \
+            router_mfma_kernel<RG, CB, ROUND, true><<<g, kRouterKWaves * kWave, 0, s>>>(x, wb, T, H, E, bias, logits, hw); \
         else                                                                                                           \
             router_mfma_kernel<RG, CB, ROUND, false><<<g, kRouterKWaves * kWave, 0, s>>>(x, wb, T, H, E, bias, logits, nullptr); \
-        return hipGetLastError();                                                                                      \
+        return finish();                                                                                               \
     }
         if (size_t(T) * E > kRouterWide) ROUTER_MFMA(2, 4, 4)
         ROUTER_MFMA(1, 2, 8)

@@ -114,6 +114,21 @@ def test_route_wide_tiles(T, E, H, norm):
     check_route(x, wr.view(torch.int16).numpy().view(np.uint16), synth.BF16, 4, bias=bias, norm=norm)
 
 
+def test_route_normalises_in_place():
+    """x_norm on top of x, sixteen tokens and more (one launch forms the norm and the logits otherwise)."""
+    rng = np.random.default_rng(5)
+    T, E, H = 37, 130, 384
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    wr = dev(0.02 * rng.standard_normal((E, H)).astype(np.float32)).to(torch.bfloat16)
+    xd = dev(x)
+    h = torch.empty_like(xd)
+    z, ids, w = moe.moe_route_topk(xd, wr, synth.BF16, 4, rmsnorm=True, x_norm=h)
+    z2, ids2, w2 = moe.moe_route_topk(xd, wr, synth.BF16, 4, rmsnorm=True, x_norm=xd)
+    moe.moe_sync_check()
+    assert torch.equal(z, z2) and torch.equal(ids, ids2) and torch.equal(w, w2)
+    assert normwise(xd.cpu().numpy(), oracle.rmsnorm(x)) <= 1e-6 and normwise(h.cpu().numpy(), oracle.rmsnorm(x)) <= 1e-6
+
+
 @pytest.mark.parametrize("E,k", [(16, 16), (256, 1), (256, 16), (64, 3), (130, 5)])
 def test_route_ties_and_edge_k(E, k):
     rng = np.random.default_rng(E + k)
