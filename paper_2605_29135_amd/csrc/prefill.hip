@@ -230,12 +230,13 @@ struct Round {
     static constexpr int B16 = DT == INT4 ? 1 : SEG / 8;  // 16-byte weight loads per lane and column block
 };
 
-// The int4 gate/up GEMM.  tmp = A (136 + Q)^T - 136 * S_m on the matrix cores (the accumulators start from -136
-// times the row's group sum), then acc += s_n * tmp.  Bound by the vector cache's address lookups, the latency of a
+// The int4 gate/up GEMM: per round, tmp = A (136 + Q)^T on the matrix cores, then acc += s_n * (tmp - 136 * S_m) (see
+// prefill_gemm_kernel).  Bound by the vector cache's address lookups, the latency of a
 // round's loads and the unpacking more than by the matrix cores: so A rows are staged by consecutive threads (a load
 // instruction touches 8 cache lines instead of 32), and the scales and group sums of 16 rounds are staged at once
 // instead of five small loads per round; and each row's token is divided out once per row, not per thread and load.
-// 2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> about 155 us.
+// 2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> about 161 us (155 with accumulators that start
+// from -136 S_m, which round otherwise than the down GEMM's fold: outputs 1.2e-4 apart, the same error).
 // Measured and not kept: weights two rounds ahead (spills: 227 us), 80- and 96-row tiles of 128 columns in two or
 // three blocks per compute unit (254-270 us), products and unpacking interleaved by scheduling groups (222 us), the
 // same staging in the down GEMM (112-135 against 103 us: its four rounds per block are mostly start-up) and, for bf16,
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int
     constexpr int LPR = R::BK / 8;              // threads per A row when staging: 16 bytes each
     constexpr int RPI = kBlock / LPR, AI = kTileM / RPI;  // A rows per load of the block, loads per round
     __shared__ __align__(16) uint16_t As[2][kTileM * R::LDS];
-    __shared__ __align__(16) float Ss[kMetaRounds][kTileM];  // -136 x group sums of the tile rows
+    __shared__ __align__(16) float Ss[kMetaRounds][kTileM];  // group sums of the tile rows
     __shared__ uint16_t Sc[kMetaRounds][kTileN];             // the columns' scales
     __shared__ float Sred[4][kTileM];                        // epilogue: per-wave activation sums
     __shared__ int atok[kTileM];                             // token of each tile row (padding: row 0's)
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int
 #pragma unroll
         for (int q = 0; q < NR; ++q) Sc[q][tid] = v[q];
 #pragma unroll
-        for (int q = 0; q < NR / 4; ++q) Ss[4 * q + tid / kTileM][row] = -136.f * f[q];
+        for (int q = 0; q < NR / 4; ++q) Ss[4 * q + tid / kTileM][row] = f[q];
     };
     auto stage_meta = [&](int r0) __attribute__((always_inline)) {
         if (KG - r0 > 4) stage_rounds(r0, std::integral_constant<int, kMetaRounds>{});
@@ -340,27 +341,27 @@ __global__ __launch_bounds__(kBlock, 2) void prefill_gateup_i4_kernel(int T, int
     #pragma unroll
                     for (int i = 0; i < MB; ++i)
                         a[i] = *reinterpret_cast<const bf16x8 *>(&As[buf][(16 * i + lr) * R::LDS + R::SEG * lg + 8 * s]);
-                    floatx4 s0[MB];  // rows of this lane: m = 16i + 4lg + q
-                    if (s == 0)
-    #pragma unroll
-                        for (int i = 0; i < MB; ++i)
-                            s0[i] = *reinterpret_cast<const floatx4 *>(&Ss[r % kMetaRounds][16 * i + 4 * lg]);
     #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const uint32_t d = s == 0 ? cb[j].x : s == 1 ? cb[j].y : s == 2 ? cb[j].z : cb[j].w;
                         const bf16x8 b = int4_offset8(d);
     #pragma unroll
                         for (int i = 0; i < MB; ++i)
-                            tmp[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, s == 0 ? s0[i] : tmp[i][j], 0, 0, 0);
+                            tmp[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                a[i], b, s == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : tmp[i][j], 0, 0, 0);
                     }
                 }
+                float cs[4];
     #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float cs = bf16_bits_to_float(Sc[r % kMetaRounds][wave * kWaveN + 16 * j + lr]);
+                for (int j = 0; j < 4; ++j) cs[j] = bf16_bits_to_float(Sc[r % kMetaRounds][wave * kWaveN + 16 * j + lr]);
     #pragma unroll
-                    for (int i = 0; i < MB; ++i)
+                for (int i = 0; i < MB; ++i) {
+                    const floatx4 sv = *reinterpret_cast<const floatx4 *>(&Ss[r % kMetaRounds][16 * i + 4 * lg]);
     #pragma unroll
-                        for (int q = 0; q < 4; ++q) acc[i][j][q] = fmaf(cs, tmp[i][j][q], acc[i][j][q]);
+                    for (int j = 0; j < 4; ++j)
+    #pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            acc[i][j][q] = fmaf(cs[j], tmp[i][j][q], fmaf(-136.f * cs[j], sv[q], acc[i][j][q]));
                 }
             }
             if (r + 1 < KG) {

@@ -13,6 +13,7 @@ import torch
 import oracle
 import paper_2605_29135_amd as moe
 import synth
+from blobs import decode_blob
 
 pytestmark = pytest.mark.gpu
 
@@ -959,6 +960,49 @@ def test_prefill_plan_and_reduction_edges(T, E, k, H, I, dtype, shared):
     pick = np.r_[0, T - 1, rng.integers(0, T, 200)]
     ref = oracle.moe_ffn(x[pick], ids[pick], w[pick].astype(np.float64), ex, H, I, dtype, sh)
     assert normwise(y[pick], ref) <= PREFILL_TOL[dtype]
+
+
+def test_prefill_int4_group_fold():
+    """The int4 prefill GEMMs fold a quantisation group as acc = fma(s, A (136 + Q)^T, fma(-136 s, S, acc)): two
+    fp32 roundings per group around exact sums.  Hidden values of 504..510 make every matrix-core sum and S whole
+    numbers below 2^24, and weights that sum to zero in each group leave results small beside 136 S, so that
+    another place for the offset shows in the third digit.  The arithmetic is repeated here in numpy; what is left
+    is the fast exp and reciprocal, which turn a few of the bf16 activations (2^-9 each of 128): 5e-4 normwise."""
+    H, I, E, k, T = 512, 128, 3, 2, 70
+    wl = synth.Workload("int4 fold", H=H, E=E, k=k, I=I, dtype=synth.INT4G128, router_dtype=synth.F32, cfg_id=610)
+    rng = np.random.default_rng(610)
+    KG = H // 128
+    q = rng.integers(-7, 8, (E, 2 * I, KG, 64))
+    q = rng.permuted(np.concatenate([q, -q], axis=3), axis=3)
+    sc = synth.bf16_bits(rng.uniform(0.008, 0.016, (E, 2 * I, KG)).astype(np.float32))
+    ex = _experts(wl)[0].copy()
+    lay = synth.blob_layout(H, I, synth.INT4G128)
+    nib = (q.reshape(E, -1) & 15).astype(np.uint8)
+    for name, raw in (("gu_q", nib[:, 0::2] | (nib[:, 1::2] << 4)), ("gu_s", sc.reshape(E, -1).view(np.uint8))):
+        o, _, n = lay[name]
+        ex[:, o:o + n] = raw
+    x = (504 + 2 * rng.integers(0, 4, (T, H))).astype(np.float32)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    w = rng.random((T, k)).astype(np.float32)
+
+    s = synth.bf16_to_f32(sc).astype(np.float64).reshape(E, 2 * I, KG)
+    xg = x.astype(np.float64).reshape(T, KG, 128)
+    ref = np.zeros((T, H))
+    for e in range(E):
+        acc = np.zeros((T, 2 * I), np.float32)
+        for g in range(KG):
+            tmp = xg[:, g] @ (136.0 + q[e, :, g]).T
+            assert tmp.max() < 2 ** 24
+            S = xg[:, g].sum(1)[:, None]
+            inner = (-136.0 * s[e, :, g] * S + acc).astype(np.float32)
+            acc = (s[e, :, g] * tmp + inner.astype(np.float64)).astype(np.float32)
+        a = acc.astype(np.float64)
+        a = a[:, 0::2] / (1 + np.exp(-a[:, 0::2])) * a[:, 1::2]
+        a = synth.bf16_to_f32(synth.bf16_bits(a.astype(np.float32))).astype(np.float64)
+        y = a @ decode_blob(ex[e], H, I, synth.INT4G128)[1].T
+        for j in range(k):
+            ref += (w[:, j] * (ids[:, j] == e))[:, None] * y
+    assert normwise(run_prefill(wl, x, ids, w, ex, None), ref) <= 5e-4
 
 
 def test_prefill_config5_chunk():
