@@ -74,14 +74,15 @@ constexpr int kBatchGrid = 256;  // one persistent block per compute unit
 // byte offset from `pool` and its key; each pair's key (-1: a pair that contributes nothing).  A group holds
 // at most 16 pairs: an expert has more only where tokens name it twice, and then takes several groups.
 struct BatchGroups {
+    alignas(16) int ids[kMaxPairs];  // (read four at a time)
     int n;
     long long off[kMaxPairs + 1];
     int group_key[kMaxPairs + 1];  // -1: the shared expert's group (every token)
     int key[kMaxPairs];            // 16 * expert + (the pair's rank among its expert's pairs) / 16
-    int ids[kMaxPairs];
     float weight[kMaxPairs];
     int per_wave[kMaxPairs / kWave];
 };
+static_assert(offsetof(BatchGroups, ids) % 16 == 0 && alignof(BatchGroups) % 16 == 0);
 
 __device__ __forceinline__ void find_groups(BatchGroups &G, int P, int E, const int32_t *__restrict__ ids,
                                             const int32_t *__restrict__ slot_of, const float *__restrict__ weights,
