@@ -47,15 +47,16 @@ __device__ __forceinline__ void split3(const float *v, bf16x8 &t1, bf16x8 &t2, b
     t3 = __builtin_bit_cast(bf16x8, make_uint4(c[0], c[1], c[2], c[3]));
 }
 
-// The eight signed nibbles q of a dword as bf16 24 + q (exact), in the order 0,4,1,5,2,6,3,7: a nibble shifted
-// to the top of the mantissa of 16, its sign bit flipped, is 16 + (q + 8).  One shift and one three-input bit
-// operation per two weights (the conversion instruction for a nibble took half of the kernel's time).  The
-// sums start from -24 times the sum of the other factors instead of zero.
-constexpr uint32_t kMinusBias2 = 0xc1c0c1c0u;  // two bf16 -24
-__device__ __forceinline__ bf16x8 nibbles_biased(uint32_t v) {
-    constexpr uint32_t m = 0x00780078u, f = 0x41c041c0u;
-    return __builtin_bit_cast(bf16x8, make_uint4(((v << 3) & m) ^ f, ((v >> 1) & m) ^ f, ((v >> 5) & m) ^ f,
-                                                 ((v >> 9) & m) ^ f));
+// The eight signed nibbles q of a dword as bf16 q / 16 (exact), in the order 0,4,1,5,2,6,3,7.  Two bit operations per
+// pair give 24 + q instead, but sums that carry 24 times the sum of the other factors round at that size: 9 tokens,
+// H 2048, I 2048, top-16 + shared: 2.4e-7 from 64 bits in 227 us, q / 16: 1.7e-7 in 231 us, one wave per row pair: 2.2e-7
+// in 495 us (16 tokens, I 512, top-8 of 256 + shared: 54, 57 and 135 us).
+__device__ __forceinline__ bf16x8 nibbles_16th(uint32_t v) {
+    uint32_t p[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        p[e] = high_halves(__builtin_amdgcn_cvt_off_f32_i4(int(v >> (4 * e))), __builtin_amdgcn_cvt_off_f32_i4(int(v >> (4 * e + 16))));
+    return __builtin_bit_cast(bf16x8, make_uint4(p[0], p[1], p[2], p[3]));
 }
 
 // How a block walks an expert's gate/up matrix.  A step is one 16-byte weight load per lane and 16-row tile:
@@ -147,7 +148,7 @@ __device__ __forceinline__ void find_groups(BatchGroups &G, int P, int E, const 
 // act[p, i] = w_p * silu(W_g[i] . x_t) * (W_u[i] . x_t) for every (token, rank) pair p and the shared expert.
 // Each block takes a contiguous share of the (expert, row tiles) items and streams their weights: the next
 // item's are in flight while this one is multiplied, and the expert's tokens stay in registers from item to
-// item.  The waves' partial products are added through LDS in wave order.  The weights (int4: as bf16 24 + q,
+// item.  The waves' partial products are added through LDS in wave order.  The weights (int4: as bf16 q / 16,
 // the scale applied to each quantisation group's fp32 sum) meet the tokens' values as three bf16 terms, so
 // that every product is exact and only the order of the fp32 sums differs from a row-wise dot product.
 // Bound by HBM (large batches) or by the latency of a few items per block (small ones).  Measured against one
@@ -225,7 +226,6 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
     };
 
     bf16x8 xt[CS][SUB][3];
-    floatx4 hi0[DT == INT4 ? CS : 1], lo0[DT == INT4 ? CS : 1];  // int4: -24 times the tokens' group sums
     floatx4 lead[CH][MT], tail[MT];
     int cnt = 0, g_at = -1;
     auto process = [&](Weights &b, const Unit &u, Weights &next, const Unit &un) __attribute__((always_inline)) {
@@ -278,16 +278,6 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
                     const float v[8] = {a.x, a.y, a.z, a.w, bq.x, bq.y, bq.z, bq.w};
                     split3<DT == INT4>(v, xt[r][d][0], xt[r][d][1], xt[r][d][2]);
                 }
-                if constexpr (DT == INT4) {
-                    const bf16x8 m = __builtin_bit_cast(bf16x8, make_uint4(kMinusBias2, kMinusBias2, kMinusBias2, kMinusBias2));
-                    hi0[r] = lo0[r] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int d = 0; d < SUB; ++d) {
-                        hi0[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][0], m, hi0[r], 0, 0, 0);
-                        lo0[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][2], m, lo0[r], 0, 0, 0);
-                        lo0[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][1], m, lo0[r], 0, 0, 0);
-                    }
-                }
             }
         }
         load(next, un);
@@ -319,17 +309,17 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
                     lead[r % CH][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][0][0], w, lead[r % CH][j], 0, 0, 0);
                     tail[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][0][1], w, tail[j], 0, 0, 0);
                 } else {
-                    floatx4 hi = hi0[r], lo = lo0[r];
+                    floatx4 hi = {0.f, 0.f, 0.f, 0.f}, lo = hi;
 #pragma unroll
                     for (int d = 0; d < SUB; ++d) {
-                        const bf16x8 w = nibbles_biased(wv[d]);
+                        const bf16x8 w = nibbles_16th(wv[d]);
                         lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][2], w, lo, 0, 0, 0);
                         hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][0], w, hi, 0, 0, 0);
                         lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[r][d][1], w, lo, 0, 0, 0);
                     }
                     const float sc = bf16_bits_to_float(b.sc[r][j]);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) lead[0][j][q] = fmaf(sc, hi[q] + lo[q], lead[0][j][q]);
+                    for (int q = 0; q < 4; ++q) lead[0][j][q] = fmaf(sc, 16.f * (hi[q] + lo[q]), lead[0][j][q]);
                 }
             }
         }

@@ -266,6 +266,40 @@ def test_ffn_batch_widths(dtype, H):
         assert check_ffn(wl, x, ids[:, :1], w[:, :1], ex, None) <= bound
 
 
+def zero_sum_gateup(ex, H, I, rng, scales=None):
+    """The int4 blobs with gate/up nibbles that sum to zero in each quantisation group (and other scales); also
+    returns the nibbles [E, 2I, H/128, 128]."""
+    ex, lay = ex.copy(), synth.blob_layout(H, I, synth.INT4G128)
+    q = rng.integers(-7, 8, (len(ex), 2 * I, H // 128, 64))
+    q = rng.permuted(np.concatenate([q, -q], axis=3), axis=3)
+    nib = (q.reshape(len(ex), -1) & 15).astype(np.uint8)
+    for name, raw in (("gu_q", nib[:, 0::2] | (nib[:, 1::2] << 4)), ("gu_s", scales)):
+        o, _, n = lay[name]
+        if raw is not None:
+            ex[:, o:o + n] = raw.reshape(len(ex), -1).view(np.uint8)
+    return ex, q
+
+
+@pytest.mark.parametrize("offset", [0.0, 64.0, 1000.0])
+def test_ffn_int4_batch_rounding(offset):
+    """Several tokens on int4 experts where the down projection keeps fp32 activations (sixteen ranks' rows exceed its
+    LDS form), so that the gate/up sums' rounding shows: hidden values around zero, and with a common offset over
+    weights that sum to zero, where a form that carries a multiple of the hidden values' sum rounds at its size
+    (24 times it: 1.5e-6 and 1.6e-5).  Exact products and fp32 sums: a few 2^-24 for gate, up and the down rows' 1920
+    products each, 6e-7 normwise."""
+    wl = synth.Workload("int4 rounding", H=512, E=16, k=16, I=1920, dtype=synth.INT4G128, router_dtype=synth.F32,
+                        cfg_id=620)
+    rng = np.random.default_rng(620)
+    ex, _ = zero_sum_gateup(_experts(wl)[0], wl.H, wl.I, rng)
+    errs = []
+    for T in (2, 7):
+        x = (offset + rng.standard_normal((T, wl.H))).astype(np.float32)
+        ids = np.argsort(rng.random((T, wl.E)), axis=1).astype(np.int32)
+        w = rng.random((T, wl.k)).astype(np.float32)
+        errs.append(check_ffn(wl, x, ids, w, ex, None))
+    assert max(errs) <= 6e-7
+
+
 @pytest.mark.parametrize("dtype,H", [(synth.F32, 384), (synth.BF16, 256), (synth.BF16, 640), (synth.BF16, 3968),
                                      (synth.BF16, 4096), (synth.INT4G128, 256), (synth.INT4G128, 2176),
                                      (synth.INT4G128, 4224)])
@@ -972,15 +1006,8 @@ def test_prefill_int4_group_fold():
     wl = synth.Workload("int4 fold", H=H, E=E, k=k, I=I, dtype=synth.INT4G128, router_dtype=synth.F32, cfg_id=610)
     rng = np.random.default_rng(610)
     KG = H // 128
-    q = rng.integers(-7, 8, (E, 2 * I, KG, 64))
-    q = rng.permuted(np.concatenate([q, -q], axis=3), axis=3)
     sc = synth.bf16_bits(rng.uniform(0.008, 0.016, (E, 2 * I, KG)).astype(np.float32))
-    ex = _experts(wl)[0].copy()
-    lay = synth.blob_layout(H, I, synth.INT4G128)
-    nib = (q.reshape(E, -1) & 15).astype(np.uint8)
-    for name, raw in (("gu_q", nib[:, 0::2] | (nib[:, 1::2] << 4)), ("gu_s", sc.reshape(E, -1).view(np.uint8))):
-        o, _, n = lay[name]
-        ex[:, o:o + n] = raw
+    ex, q = zero_sum_gateup(_experts(wl)[0], H, I, rng, sc)
     x = (504 + 2 * rng.integers(0, 4, (T, H))).astype(np.float32)
     ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
     w = rng.random((T, k)).astype(np.float32)
