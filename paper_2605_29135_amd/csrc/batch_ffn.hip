@@ -59,6 +59,29 @@ __device__ __forceinline__ bf16x8 nibbles_16th(uint32_t v) {
     return __builtin_bit_cast(bf16x8, make_uint4(p[0], p[1], p[2], p[3]));
 }
 
+// One row's dot product in fp32, element by element: what a sum of three-term products that is not finite is taken
+// from.  Those terms give NaN for an infinite factor (inf - inf in the split, 0 times inf in a term that is zero or
+// a step past the wave's share) and can overflow on the way; a row-wise dot product gives what the factors give.
+template <int DT>
+__device__ __forceinline__ float row_dot(const uint8_t *blob, int row, const float *x, int H, int I) {
+    const uint8_t *w = blob + row * row_bytes_of(DT, H);
+    const auto *sc = reinterpret_cast<const uint16_t *>(blob + size_t(I) * H) + size_t(row) * (H / 128);  // (int4)
+    float acc = 0.f;
+#pragma unroll 1
+    for (int c = 0; c < H; c += 32) {
+        float part = 0.f;
+#pragma unroll 1
+        for (int h = c; h < c + 32; ++h) {
+            float v;
+            if constexpr (DT == BF16) v = bf16_bits_to_float(reinterpret_cast<const uint16_t *>(w)[h]);
+            else v = float(int(__builtin_amdgcn_sbfe(uint32_t(w[h / 2]), 4 * (h & 1), 4)));
+            part = fmaf(v, x[h], part);
+        }
+        acc += DT == INT4 ? bf16_bits_to_float(sc[c / 128]) * part : part;
+    }
+    return acc;
+}
+
 // How a block walks an expert's gate/up matrix.  A step is one 16-byte weight load per lane and 16-row tile:
 // lane (lr = l % 16, lg = l / 16) holds row lr, elements STEP / 4 * lg onward of the step, and the same
 // elements of token lr.  An item is TILES tiles of one expert; its eight waves take contiguous shares of the
@@ -350,6 +373,11 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
             }
             const int p = mem[col];
             const float wp = p < P ? G.weight[p] : 1.f;
+            if (!(fabsf(gate) < INFINITY && fabsf(up) < INFINITY)) {
+                const float *xt = x + size_t(p < P ? p / k : p - P) * H;
+                gate = row_dot<DT>(pool + G.off[g], row0 + 2 * i, xt, H, I);
+                up = row_dot<DT>(pool + G.off[g], row0 + 2 * i + 1, xt, H, I);
+            }
             act[size_t(p) * I + row0 / 2 + i] = wp * (gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate)) * up);
         }
     };

@@ -300,6 +300,74 @@ def test_ffn_int4_batch_rounding(offset):
     assert max(errs) <= 6e-7
 
 
+def run_ffn(wl, x, ids, w, ex, sh=None):
+    y = moe.moe_expert_ffn_grouped(dev(x), dev(ids), dev(w), dev(ex.reshape(-1)), ex.shape[1], wl.dtype, wl.I, wl.E,
+                                   shared_w=None if sh is None else dev(sh))
+    moe.moe_sync_check()
+    return y.cpu().numpy()
+
+
+def test_ffn_batch_infinite_weight_and_values():
+    """Several tokens on bf16 experts: an infinite gate weight in the last columns (where waves with a ragged share load
+    past it, and a hidden value of 1 has zero second and third terms) makes the outputs of its expert's tokens
+    infinite, as a row-wise dot product has it; an infinite or NaN hidden value stays with its token."""
+    wl = synth.Workload("infinities", H=1152, E=6, k=2, I=128, dtype=synth.BF16, router_dtype=synth.F32, cfg_id=630)
+    rng = np.random.default_rng(630)
+    ids = np.array([[0, 1], [2, 3], [1, 2], [0, 4], [4, 5], [5, 3], [3, 0], [2, 4]], np.int32)
+    w = rng.random(ids.shape).astype(np.float32) + 0.1
+    x = rng.standard_normal((8, wl.H)).astype(np.float32)
+    x[:, -1] = 1.0
+    clean = _experts(wl)[0]
+    ex = clean.copy()
+    ex[0, :4 * wl.I * wl.H].view(np.uint16).reshape(2 * wl.I, wl.H)[34, -1] = 0x7F80
+    hit = (ids == 0).any(1)
+    with np.errstate(invalid="ignore"):
+        ref = oracle.moe_ffn(x, ids, w.astype(np.float64), ex, wl.H, wl.I, wl.dtype)
+    assert np.isinf(ref[hit]).all()
+    y = run_ffn(wl, x, ids, w, ex)
+    assert (y[hit] == ref[hit]).all() and normwise(y[~hit], ref[~hit]) <= 1e-5
+    for bad in (np.inf, np.nan):
+        xb = x.copy()
+        xb[5, 40] = bad
+        y = run_ffn(wl, xb, ids, w, clean)
+        ok = np.arange(8) != 5
+        ref = oracle.moe_ffn(x[ok], ids[ok], w[ok].astype(np.float64), clean, wl.H, wl.I, wl.dtype)
+        assert not np.isfinite(y[5]).any() and normwise(y[ok], ref) <= 1e-5
+
+
+def test_ffn_int4_batch_infinite_scale_and_large_values():
+    """Several tokens on int4 experts, the down projection in fp32: an infinite scale in the last quantisation group
+    (hidden values of the nibbles' signs there: +inf from every part of a row-wise sum), and hidden values near 2^120
+    on scales that bring the sums back to a few units."""
+    wl = synth.Workload("int4 range", H=1152, E=16, k=16, I=1920, dtype=synth.INT4G128, router_dtype=synth.F32,
+                        cfg_id=631)
+    H, I = wl.H, wl.I
+    rng = np.random.default_rng(631)
+    ids = np.argsort(rng.random((3, wl.E)), axis=1).astype(np.int32)
+    w = rng.random(ids.shape).astype(np.float32) + 0.1
+    x = rng.standard_normal((3, H)).astype(np.float32)
+    ex = _experts(wl)[0].copy()
+    lay = synth.blob_layout(H, I, synth.INT4G128)
+    scales = ex[:, lay["gu_s"][0]:lay["gu_s"][0] + lay["gu_s"][2]].view(np.uint16).reshape(wl.E, 2 * I, H // 128)
+
+    small = ex.copy()
+    o, _, n = lay["gu_s"]
+    small[:, o:o + n] = synth.bf16_bits(synth.bf16_to_f32(scales) * np.float32(2.0 ** -118)).reshape(wl.E, -1).view(np.uint8)
+    big = x * np.float32(2.0 ** 120)
+    ref = oracle.moe_ffn(big, ids, w.astype(np.float64), small, H, I, wl.dtype)
+    assert normwise(run_ffn(wl, big, ids, w, small), ref) <= 1e-5
+
+    row = ex[2, 34 * H // 2:35 * H // 2]  # (gate row 17 of expert 2)
+    row[-64:] = np.where(row[-64:] % 16 == 0, row[-64:] + 1, row[-64:])
+    row[-64:] = np.where(row[-64:] // 16 == 0, row[-64:] + 16, row[-64:])
+    scales[2, 34, -1] = 0x7F80
+    ex[:, o:o + n] = scales.reshape(wl.E, -1).view(np.uint8)
+    x[:, -128:] = np.abs(x[:, -128:]) * np.sign(synth.unpack_int4(row[-64:]))
+    ref = oracle.moe_ffn(x, ids, w.astype(np.float64), ex, H, I, wl.dtype)
+    y = run_ffn(wl, x, ids, w, ex)
+    assert np.isinf(ref).any() and (np.isinf(ref) == np.isinf(y)).all() and (y[np.isinf(ref)] == ref[np.isinf(ref)]).all()
+
+
 @pytest.mark.parametrize("dtype,H", [(synth.F32, 384), (synth.BF16, 256), (synth.BF16, 640), (synth.BF16, 3968),
                                      (synth.BF16, 4096), (synth.INT4G128, 256), (synth.INT4G128, 2176),
                                      (synth.INT4G128, 4224)])
