@@ -101,8 +101,8 @@ struct BatchGroups {
     alignas(16) int ids[kMaxPairs];  // (read four at a time)
     int n;
     long long off[kMaxPairs + 1];
-    int group_key[kMaxPairs + 1];  // -1: the shared expert's group (every token)
-    int key[kMaxPairs];            // 16 * expert + (the pair's rank among its expert's pairs) / 16
+    long long group_key[kMaxPairs + 1];  // -1: the shared expert's group (every token)
+    long long key[kMaxPairs];            // 16 * expert + (the pair's rank among its expert's pairs) / 16
     float weight[kMaxPairs];
     int per_wave[kMaxPairs / kWave];
 };
@@ -130,7 +130,7 @@ __device__ __forceinline__ void find_groups(BatchGroups &G, int P, int E, const 
     }
     __syncthreads();
     bool first = false;
-    int key = -1;
+    long long key = -1;
     unsigned long long firsts = 0;
     if (tid < kMaxPairs) {
         int rank = 0;
@@ -140,7 +140,7 @@ __device__ __forceinline__ void find_groups(BatchGroups &G, int P, int E, const 
             const int4 o = v[q / 4];
             rank += (o.x == e && q < tid) + (o.y == e && q + 1 < tid) + (o.z == e && q + 2 < tid) + (o.w == e && q + 3 < tid);
         }
-        if (s >= 0) key = 16 * e + rank / 16;
+        if (s >= 0) key = 16ll * e + rank / 16;
         G.key[tid] = key;
         first = s >= 0 && rank % 16 == 0;
         firsts = __ballot(first);
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
         const bool fresh = g != g_at;
         if (fresh) {
             g_at = g;
-            const int gk = G.group_key[g];
+            const long long gk = G.group_key[g];
             if (gk < 0) {
                 cnt = T;
                 if (lane < T) mem[lane] = P + lane;

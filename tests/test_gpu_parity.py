@@ -335,6 +335,28 @@ def test_ffn_batch_infinite_weight_and_values():
         assert not np.isfinite(y[5]).any() and normwise(y[ok], ref) <= 1e-5
 
 
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.INT4G128])
+def test_ffn_batch_many_expert_ids(dtype):
+    """Ids near and above 2^27 (a call takes any number of experts): three that would be one, or the shared expert, if
+    sixteen times the id were held in 32 bits."""
+    wl = synth.Workload("large ids", H=256, E=4, k=3, I=128, dtype=dtype, router_dtype=synth.F32, shared=True,
+                        cfg_id=640 + dtype)
+    ex, sh = _experts(wl)
+    rng = np.random.default_rng(640)
+    far = np.array([5, 2 ** 28 + 5, 2 ** 27 + 6, 2 ** 28 + 9], np.int32)
+    E = 2 ** 28 + 10
+    slot_of = torch.full((E,), -1, dtype=torch.int32, device=DEV)
+    slot_of[torch.from_numpy(far).long().to(DEV)] = torch.arange(4, dtype=torch.int32, device=DEV)
+    x = rng.standard_normal((7, wl.H)).astype(np.float32)
+    ids = np.argsort(rng.random((7, 4)), axis=1)[:, :3].astype(np.int32)
+    w = rng.random(ids.shape).astype(np.float32)
+    y = moe.moe_expert_ffn_grouped(dev(x), dev(far[ids]), dev(w), dev(ex.reshape(-1)), wl.expert_bytes, wl.dtype, wl.I, E,
+                                   slot_of=slot_of, shared_w=dev(sh))
+    moe.moe_sync_check()
+    ref = oracle.moe_ffn(x, ids, w.astype(np.float64), ex, wl.H, wl.I, wl.dtype, sh)
+    assert normwise(y.cpu().numpy(), ref) <= 1e-3
+
+
 def test_ffn_int4_batch_infinite_scale_and_large_values():
     """Several tokens on int4 experts, the down projection in fp32: an infinite scale in the last quantisation group
     (hidden values of the nibbles' signs there: +inf from every part of a row-wise sum), and hidden values near 2^120
