@@ -1,9 +1,11 @@
-// batch_ffn.hip -- the expert FFN of 2 to 16 decode tokens on the matrix cores (gfx950).
+// batch_ffn.hip -- the gate/up half of the expert FFN of 2 to 16 decode tokens (gfx950).
 //
 // A decode batch is bound by the bytes of the distinct experts that it selects (61 on average for 16
-// tokens of top-8 over 256 Zipf-routed experts: 384 MB of bf16).  A weight tile is loaded once, straight
-// into registers in the matrix-core lane layout, and multiplied with all of its expert's tokens at once,
-// so that a wave has nothing to do per token and its loads stay in flight.
+// tokens of top-8 over 256 Zipf-routed experts: 384 MB of bf16).  Two kernels read each weight once:
+// on the matrix cores a weight tile is loaded straight into registers in their lane layout and multiplied
+// with all of its expert's tokens at once, so that a wave has nothing to do per token and its loads stay in
+// flight; with one wave per row pair the tokens follow one another, and a block starts after two dependent
+// loads instead of a search over all the pairs.  rows_faster() says which call takes which.
 #include "internal.h"
 #include "device_common.h"
 
@@ -16,9 +18,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxPairs = MOE_MAX_DECODE_TOKENS * MOE_MAX_TOPK;  // (token, rank) pairs of a call
-
-constexpr int kRowsMaxTokens = 5;  // bf16 experts: up to this many tokens one wave per row pair is the faster way (H 2048,
-                                   // I 768, top-8 of 128: 2 tokens 28.0 against 31.5 us, 4 44.3 against 46.7, 6 60.3 against 59.6, 12 102.8 against 94.7)
 
 // High halves of two floats as a bf16 pair (lo's in the low half).
 __device__ __forceinline__ uint32_t high_halves(float lo, float hi) {
@@ -391,12 +390,15 @@ __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
     }
 }
 
-// fp32 experts, and bf16 ones of up to kRowsMaxTokens tokens: one wave per row pair (gate row 2i, up row 2i + 1),
-// its weights loaded once and applied to each token of the expert (fp32 matrix instructions measured no faster here, and their longer chains of roundings
+// One wave per row pair (gate row 2i, up row 2i + 1): its weights are loaded once and applied to each token of the
+// expert (fp32 experts always: fp32 matrix instructions measured no faster here, and their longer chains of roundings
 // less exact).  Block (row pairs, p): for all the pairs of pair p's expert if p is the first of them (the
 // other blocks leave: each wave finds the expert's pairs by ballots over the ids, so that no launch groups
 // them first: 5.3 us of the 31.8 us of 7 tokens at H 1408, I 384); p = T * k is the shared expert.
-template <int DT, int NCH, bool FULL>
+// NCH is a row's exact number of 64-lane chunks (H 2560, bf16, 16 tokens of top-8 over 128 experts of I 768: 195 us
+// with eight chunks for five, 155 with five).  PACKED: the weights are unpacked anew for every token, since unpacked
+// they take twice the registers (bf16, H 4096: 216 and 2 waves per SIMD, 152 and 3; 4 tokens, I 1024: 65 -> 61 us).
+template <int DT, int NCH, bool FULL, bool PACKED>
 __global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
     const float *__restrict__ x, int T, int H, int I, int E, int k, const int32_t *__restrict__ ids,
     const int32_t *__restrict__ slot_of, const uint8_t *__restrict__ pool, size_t expert_bytes,
@@ -431,11 +433,11 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
             if (cnt == 0 && mask) first = m * kWave + int(__builtin_ctzll(mask)) == g;
             cnt += __popcll(mask);
         }
+        if (!first) return;
         if (s < 0) {
             if (blockIdx.x == 0 && tid == 0) atomicOr(err, kErrNotResident);
             return;
         }
-        if (!first) return;
         blob = pool + size_t(s) * expert_bytes;
     } else {
         cnt = T;
@@ -445,10 +447,7 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const int i = blockIdx.x * (kBlock / kWave) + wave;
-    if (i >= I) return;
     const size_t rb = row_bytes_of(DT, H);
-    const uint8_t *gate = blob + size_t(2 * i) * rb + 16 * lane;
     float xv[NCH][EPC];
     auto load_token = [&](int p) {
         const float *xt = x + size_t(p < P ? p / k : p - P) * H;
@@ -464,27 +463,66 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
         }
     };
     load_token(mem[0]);  // before the weights: loads retire in order, so waiting for x never waits for them
-    uint4 wg[NCH], wu[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const bool in = FULL || (c * kWave + lane) * EPC < H;
-        wg[c] = in ? load16_stream(gate + size_t(c) * 16 * kWave) : make_uint4(0, 0, 0, 0);
-        wu[c] = in ? load16_stream(gate + rb + size_t(c) * 16 * kWave) : make_uint4(0, 0, 0, 0);
-    }
-    for (int q = 0; q < cnt; ++q) {
-        const int p = mem[q];
-        if (q > 0) load_token(p);
-        const float wp = p < P ? weights[p] : 1.f;
-        float ga = 0.f, ua = 0.f;
+    bool again = false;
+    for (int i = blockIdx.x * (kBlock / kWave) + wave; i < I; i += gridDim.x * (kBlock / kWave), again = true) {
+        const uint8_t *gate = blob + size_t(2 * i) * rb + 16 * lane;
+        uint4 wg[NCH], wu[NCH];
+        float sg[DT == INT4 ? NCH : 1], su[DT == INT4 ? NCH : 1];
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            ga += chunk_dot<DT>(wg[c], xv[c]);
-            ua += chunk_dot<DT>(wu[c], xv[c]);
+            const int col0 = (c * kWave + lane) * EPC;
+            const bool in = FULL || col0 < H;
+            wg[c] = in ? load16_stream(gate + size_t(c) * 16 * kWave) : make_uint4(0, 0, 0, 0);
+            wu[c] = in ? load16_stream(gate + rb + size_t(c) * 16 * kWave) : make_uint4(0, 0, 0, 0);
+            if constexpr (DT == INT4) {
+                const uint16_t *sc = reinterpret_cast<const uint16_t *>(blob + size_t(I) * H) + size_t(2 * i) * (H / 128) + col0 / 128;
+                sg[c] = in ? bf16_bits_to_float(sc[0]) : 0.f;
+                su[c] = in ? bf16_bits_to_float(sc[H / 128]) : 0.f;
+            }
         }
-        ga = wave_sum(ga);
-        ua = wave_sum(ua);
-        if (lane == 0) act[size_t(p) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
+        for (int q = 0; q < cnt; ++q) {
+            const int p = mem[q];
+            if (q > 0 || (again && cnt > 1)) load_token(p);
+            const float wp = p < P ? weights[p] : 1.f;
+            float ga = 0.f, ua = 0.f;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                if constexpr (PACKED) {  // (unpacked again for every token: the compiler would keep them unpacked)
+                    uint4 &a = wg[c], &b = wu[c];
+                    asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w), "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w));
+                }
+                const float dg = chunk_dot<DT>(wg[c], xv[c]), du = chunk_dot<DT>(wu[c], xv[c]);
+                ga += DT == INT4 ? dg * sg[c] : dg;
+                ua += DT == INT4 ? du * su[c] : du;
+            }
+            ga = wave_sum(ga);
+            ua = wave_sum(ua);
+            if (lane == 0) act[size_t(p) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
+        }
     }
+}
+
+// Which kernel: one wave per row pair (true) or the matrix cores.  The matrix cores win where many of a wave's tokens
+// would follow one another; their cost is the search before the first load and steps that fill no whole pass.  Row
+// pairs / matrix cores, us for the whole FFN, each with its neighbours at other T on the same side:
+// bf16, by the tokens per expert T k / E and by T (the most chosen experts' tokens, and the shared expert's T).  H 2048,
+// I 768, top-8 of 128: 55 / 60 at 6 tokens, 92 / 93 at 12, 117 / 113 at 16 (T k / E = 1); top-4 of 16: 28.1 / 30.6 at
+// 6 (1.5), 39 / 37 at 10 (2.5); H 1024, I 1536, top-4 of 32: 41 / 43 at 10 (1.25), 56 / 54 at 16 (2).  With a shared
+// expert: H 2048, I 512, top-8 of 256: 47 / 48 at 6, 59 / 57 at 8, 102 / 90 at 16; H 1024, I 768: 44 / 46 at 7, 58 /
+// 57 at 10.  Up to H 768, and from 1025 to 1536, a quarter or more of a matrix-core pass's steps are empty: twice as
+// many (H 512, I 3072, top-4 of 32, 16 tokens: 71 / 86; H 1280, I 512, top-8 of 256 + shared, 16 tokens: 75 / 79).
+// Beyond H 2048 the matrix cores would read the tokens anew in every pass (H 2560, I 768, 16 tokens: 140 / 285).
+// int4, by blocks times the tokens that follow one another, since a row pair's products cost several times the loads
+// there: H 2048, I 128, top-1 of 16: 12.5 / 14.9 at 6 tokens (1152), 20.8 / 19.4 at 12 (4608); H 6144: 18.9 / 26.1
+// at 4 (512), 42 / 44 at 12; H 2176, I 256, top-2 of 16: 15.3 / 17.3 at 4 (2048), 20 / 19.2 at 6 (4608); with a shared
+// expert H 4096, I 128, top-2 of 8: 14.6 / 18.5 at 3 (1728), 24 / 22 at 5 (4800).
+bool rows_faster(int T, int H, int I, int E, int k, int dtype, bool shared) {
+    if (dtype == F32) return true;
+    if (dtype == INT4) return H <= 8192 && (long long)(I / 4) * T * (k + shared) * T * (1 + shared) <= 2048;
+    if (H > 2048) return true;
+    const bool idle = H <= 768 || (H > 1024 && H <= 1536);
+    const long long pairs = 40ll * T * k, limit = (shared ? 50ll : 60ll) * E * (idle ? 2 : 1);  // in units of E / 40
+    return shared ? pairs + 5ll * T * E < limit : pairs + 3ll * (T > 8 ? T - 8 : 0) * E <= limit;
 }
 
 }  // namespace
@@ -499,27 +537,48 @@ hipError_t launch_batch_gateup(const float *x, int T, int H, int I, int E, int k
                                                                        expert_bytes, shared_w, weights, act, err); \
         return hipGetLastError();                                                                              \
     }
-    if (dtype == F32 || (dtype == BF16 && T <= kRowsMaxTokens)) {
-        const dim3 grid(unsigned((I + kBlock / kWave - 1) / (kBlock / kWave)), unsigned(T * k + (shared_w ? 1 : 0)));
-        // FULL: every lane's chunk slots lie inside the row, no bound checks
-#define ROWS_CASE(DT, N)                                                                                             \
-    if (dtype == DT && H <= N * kWave * Fmt<DT>::EPC) {                                                              \
-        auto *kernel = H == N * kWave * Fmt<DT>::EPC ? batch_gateup_rows_kernel<DT, N, true> : batch_gateup_rows_kernel<DT, N, false>; \
-        kernel<<<grid, kBlock, 0, s>>>(x, T, H, I, E, k, ids, slot_of, pool, expert_bytes, shared_w, weights, act, err); \
+    if (rows_faster(T, H, I, E, k, dtype, shared_w != nullptr)) {
+        const int pairs = T * k + (shared_w ? 1 : 0), quads = (I + kBlock / kWave - 1) / (kBlock / kWave);
+        // Several row pairs per wave where a launch has several rounds of blocks: fewer prologues, and fewer blocks that
+        // leave at once (bf16, I 2048, top-8 of 64, 4 tokens: H 2048 112 -> 103 us, H 512 45.6 -> 40.7, four pairs 38.8;
+        // fp32, H 512, top-4 of 32, 16 tokens: 82 -> 73, four 76).  Not for small experts (H 1024, I 384, top-6 of 64, 16
+        // tokens: 29 -> 33) and, for longer rows, with a shared expert, whose tokens would all follow one another twice
+        // (H 2048, I 768, top-8 of 60, 4 tokens: 46 -> 49; H 512, I 768, top-8 of 64, 6 tokens: 25.5 -> 24.4).
+        const int blocks = quads * pairs;
+        const int per_wave = shared_w ? (H <= 512 && blocks >= 8192 ? 2 : 1)
+                             : I < 768 || blocks < 4096 ? 1 : dtype == BF16 && H <= 512 && I >= 2048 ? 4 : 2;
+        const dim3 grid(unsigned((quads + per_wave - 1) / per_wave), unsigned(pairs));
+#define ROWS_LAUNCH(DT, N, FULL, PACKED)                                                                             \
+    {                                                                                                                \
+        batch_gateup_rows_kernel<DT, N, FULL, PACKED><<<grid, kBlock, 0, s>>>(x, T, H, I, E, k, ids, slot_of, pool,  \
+                                                                              expert_bytes, shared_w, weights, act, err); \
         return hipGetLastError();                                                                                    \
     }
-        ROWS_CASE(F32, 1) ROWS_CASE(F32, 2) ROWS_CASE(F32, 4) ROWS_CASE(F32, 8)
-        ROWS_CASE(BF16, 1) ROWS_CASE(BF16, 2) ROWS_CASE(BF16, 4) ROWS_CASE(BF16, 8)
+    // FULL: every lane's chunk slots lie inside the row, no bound checks.  PACKED where registers limit the waves of a
+    // launch that fills the chip (bf16 rows that are not full: no; H 1792, I 512, top-6, 8 tokens: 40 against 45 us).
+#define ROWS_CASE(DT, N)                                                                                             \
+    if (dtype == DT && H <= N * kWave * Fmt<DT>::EPC) {                                                              \
+        constexpr bool kPackFull = DT == BF16 && N >= 4, kPack = DT == INT4 && N >= 2;                                \
+        if (H != N * kWave * Fmt<DT>::EPC) ROWS_LAUNCH(DT, N, false, kPack)                                          \
+        if (!kPackFull || blocks < 2048) ROWS_LAUNCH(DT, N, true, kPack)                                    \
+        ROWS_LAUNCH(DT, N, true, kPack || kPackFull)                                                                 \
+    }
+        ROWS_CASE(F32, 1) ROWS_CASE(F32, 2) ROWS_CASE(F32, 3) ROWS_CASE(F32, 4)
+        ROWS_CASE(F32, 5) ROWS_CASE(F32, 6) ROWS_CASE(F32, 7) ROWS_CASE(F32, 8)
+        ROWS_CASE(BF16, 1) ROWS_CASE(BF16, 2) ROWS_CASE(BF16, 3) ROWS_CASE(BF16, 4)
+        ROWS_CASE(BF16, 5) ROWS_CASE(BF16, 6) ROWS_CASE(BF16, 7) ROWS_CASE(BF16, 8)
+        ROWS_CASE(INT4, 1) ROWS_CASE(INT4, 2) ROWS_CASE(INT4, 3) ROWS_CASE(INT4, 4)
 #undef ROWS_CASE
+#undef ROWS_LAUNCH
         return hipErrorInvalidValue;
     }
-    // the fewest steps per wave that hold a wave's share of the reduction range (longer ranges take passes)
+    // the fewest steps per wave that hold a wave's share of the reduction range (longer int4 rows take passes)
 #define GU_CASE(DT)                                                                       \
     if (dtype == DT) {                                                                    \
         const int share = (H / Walk<DT>::STEP + kBatchWaves - 1) / kBatchWaves;           \
         if (share <= Walk<DT>::MAXS / 2) GU_LAUNCH(DT, Walk<DT>::MAXS / 2, true)          \
         if (share <= Walk<DT>::MAXS) GU_LAUNCH(DT, Walk<DT>::MAXS, true)                  \
-        GU_LAUNCH(DT, Walk<DT>::MAXS, false)                                                  \
+        if constexpr (DT == INT4) GU_LAUNCH(DT, Walk<DT>::MAXS, false)                    \
     }
     GU_CASE(BF16) GU_CASE(INT4)
 #undef GU_CASE

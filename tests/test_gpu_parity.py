@@ -256,7 +256,7 @@ def test_ffn_batch_widths(dtype, H):
                         cfg_id=300 + H + dtype)
     ex, sh = _experts(wl)
     rng = np.random.default_rng(H + dtype)
-    for T in (2, 5, 6, 16):  # (bf16: up to 5 tokens one wave per row pair, above that the matrix cores)
+    for T in (2, 5, 6, 16):  # (few tokens: one wave per row pair; many, up to H 2048 in bf16: the matrix cores)
         x = rng.standard_normal((T, wl.H)).astype(np.float32)
         ids = rng.integers(0, 3, (T, wl.k)).astype(np.int32)  # repeated within a token too: up to 30 pairs of one
         ids[0, 0] = 8
@@ -264,6 +264,35 @@ def test_ffn_batch_widths(dtype, H):
         bound = 1e-3 if dtype == synth.INT4G128 else 1e-5
         assert check_ffn(wl, x, ids, w, ex, sh, slot_perm=rng.permutation(wl.E)) <= bound
         assert check_ffn(wl, x, ids[:, :1], w[:, :1], ex, None) <= bound
+
+
+@pytest.mark.parametrize("dtype,H,I,E,k,T", [(synth.BF16, 384, 1024, 24, 8, 4), (synth.BF16, 512, 2048, 24, 6, 2),
+                                             (synth.BF16, 768, 768, 24, 8, 4),
+                                             (synth.BF16, 1536, 128, 24, 4, 5), (synth.BF16, 1792, 768, 16, 6, 4),
+                                             (synth.BF16, 2048, 768, 16, 6, 4), (synth.BF16, 2560, 128, 32, 16, 4),
+                                             (synth.BF16, 2560, 128, 8, 3, 16), (synth.BF16, 2944, 768, 12, 6, 4),
+                                             (synth.BF16, 3072, 128, 32, 16, 4), (synth.BF16, 3584, 128, 32, 16, 4),
+                                             (synth.BF16, 3584, 128, 8, 2, 3), (synth.BF16, 4096, 768, 12, 6, 4),
+                                             (synth.F32, 640, 768, 24, 8, 4), (synth.F32, 1280, 128, 8, 3, 5),
+                                             (synth.F32, 1664, 128, 8, 3, 5), (synth.F32, 1920, 768, 16, 6, 4),
+                                             (synth.INT4G128, 4096, 128, 12, 2, 4), (synth.INT4G128, 4224, 128, 12, 1, 6),
+                                             (synth.INT4G128, 6144, 128, 12, 1, 6), (synth.INT4G128, 8064, 128, 8, 1, 5),
+                                             (synth.INT4G128, 8192, 256, 8, 2, 4), (synth.INT4G128, 8320, 128, 8, 1, 3)])
+def test_ffn_batch_row_pair_chunks(dtype, H, I, E, k, T):
+    """One wave per row pair: each number of 64-lane chunks a row has, full and partly filled; launches that take one,
+    two and four row pairs per wave, few and many blocks; tokens that share experts and tokens that do not, with a
+    shared expert and without.  Bounds as above."""
+    wl = synth.Workload("row pairs", H=H, E=E, k=k, I=I, dtype=dtype, router_dtype=synth.F32, shared=H <= 512,
+                        cfg_id=340 + H + I + dtype)
+    ex, sh = _experts(wl)
+    rng = np.random.default_rng(H + I)
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    w = rng.random((T, k)).astype(np.float32)
+    bound = 1e-3 if dtype == synth.INT4G128 else 1e-5
+    for ids in (np.argsort(rng.random((T, E)), axis=1)[:, :k], rng.integers(0, 2, (T, k))):
+        assert check_ffn(wl, x, ids.astype(np.int32), w, ex, None, slot_perm=rng.permutation(E)) <= bound
+        if sh is not None:
+            assert check_ffn(wl, x, ids.astype(np.int32), w, ex, sh, slot_perm=rng.permutation(E)) <= bound
 
 
 def zero_sum_gateup(ex, H, I, rng, scales=None):
@@ -307,15 +336,16 @@ def run_ffn(wl, x, ids, w, ex, sh=None):
     return y.cpu().numpy()
 
 
-def test_ffn_batch_infinite_weight_and_values():
-    """Several tokens on bf16 experts: an infinite gate weight in the last columns (where waves with a ragged share load
+@pytest.mark.parametrize("T", [8, 10])
+def test_ffn_batch_infinite_weight_and_values(T):
+    """Several tokens on bf16 experts (8: one wave per row pair, 10: the matrix cores): an infinite gate weight in the last columns (where waves with a ragged share load
     past it, and a hidden value of 1 has zero second and third terms) makes the outputs of its expert's tokens
     infinite, as a row-wise dot product has it; an infinite or NaN hidden value stays with its token."""
     wl = synth.Workload("infinities", H=1152, E=6, k=2, I=128, dtype=synth.BF16, router_dtype=synth.F32, cfg_id=630)
     rng = np.random.default_rng(630)
-    ids = np.array([[0, 1], [2, 3], [1, 2], [0, 4], [4, 5], [5, 3], [3, 0], [2, 4]], np.int32)
+    ids = np.array([[0, 1], [2, 3], [1, 2], [0, 4], [4, 5], [5, 3], [3, 0], [2, 4], [1, 5], [4, 1]], np.int32)[:T]
     w = rng.random(ids.shape).astype(np.float32) + 0.1
-    x = rng.standard_normal((8, wl.H)).astype(np.float32)
+    x = rng.standard_normal((T, wl.H)).astype(np.float32)
     x[:, -1] = 1.0
     clean = _experts(wl)[0]
     ex = clean.copy()
@@ -330,16 +360,16 @@ def test_ffn_batch_infinite_weight_and_values():
         xb = x.copy()
         xb[5, 40] = bad
         y = run_ffn(wl, xb, ids, w, clean)
-        ok = np.arange(8) != 5
+        ok = np.arange(T) != 5
         ref = oracle.moe_ffn(x[ok], ids[ok], w[ok].astype(np.float64), clean, wl.H, wl.I, wl.dtype)
         assert not np.isfinite(y[5]).any() and normwise(y[ok], ref) <= 1e-5
 
 
-@pytest.mark.parametrize("dtype", [synth.BF16, synth.INT4G128])
-def test_ffn_batch_many_expert_ids(dtype):
+@pytest.mark.parametrize("dtype,H,T", [(synth.BF16, 256, 7), (synth.BF16, 1024, 16), (synth.INT4G128, 256, 7)])
+def test_ffn_batch_many_expert_ids(dtype, H, T):
     """Ids near and above 2^27 (a call takes any number of experts): three that would be one, or the shared expert, if
     sixteen times the id were held in 32 bits."""
-    wl = synth.Workload("large ids", H=256, E=4, k=3, I=128, dtype=dtype, router_dtype=synth.F32, shared=True,
+    wl = synth.Workload("large ids", H=H, E=4, k=3, I=128, dtype=dtype, router_dtype=synth.F32, shared=True,
                         cfg_id=640 + dtype)
     ex, sh = _experts(wl)
     rng = np.random.default_rng(640)
@@ -347,8 +377,8 @@ def test_ffn_batch_many_expert_ids(dtype):
     E = 2 ** 28 + 10
     slot_of = torch.full((E,), -1, dtype=torch.int32, device=DEV)
     slot_of[torch.from_numpy(far).long().to(DEV)] = torch.arange(4, dtype=torch.int32, device=DEV)
-    x = rng.standard_normal((7, wl.H)).astype(np.float32)
-    ids = np.argsort(rng.random((7, 4)), axis=1)[:, :3].astype(np.int32)
+    x = rng.standard_normal((T, wl.H)).astype(np.float32)
+    ids = np.argsort(rng.random((T, 4)), axis=1)[:, :3].astype(np.int32)
     w = rng.random(ids.shape).astype(np.float32)
     y = moe.moe_expert_ffn_grouped(dev(x), dev(far[ids]), dev(w), dev(ex.reshape(-1)), wl.expert_bytes, wl.dtype, wl.I, E,
                                    slot_of=slot_of, shared_w=dev(sh))
