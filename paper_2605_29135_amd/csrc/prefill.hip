@@ -102,11 +102,10 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
     __shared__ int off[MOE_MAX_EXPERTS + 2], toff[MOE_MAX_EXPERTS + 2];
     const int P = T * k, G = E + 1, tid = threadIdx.x;
     for (int g = tid; g < G; g += kPlanThreads) {
-        cnt[g] = 0;
+        cnt[g] = g == E && has_shared ? T : 0;
         cur[g] = 0;
         slot[g] = g == E ? -2 : (slot_of ? slot_of[g] : g);
     }
-    __syncthreads();
     // A pair's expert (or -1): a bad id or an absent slot raises the flag and zeroes the pair's output row.
     auto checked = [&](int e, int p) {
         if (e >= 0 && e < E && slot[e] >= 0) return e;
@@ -114,21 +113,87 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
         for (int h = 0; h < H; ++h) ws.y_part[size_t(p) * H + h] = 0.f;
         return -1;
     };
-    // Up to 16384 pairs: a thread's 16 ids are loaded together and stay in registers with their ranks within their
-    // experts' groups (one load latency and one pass of LDS atomics, where a load per 1024 pairs and two passes took
-    // 25 us for 2048 tokens of top-8).  More pairs: two passes, eight ids loaded together.
-    const bool kept = P <= kPlanKeep * kPlanThreads;
-    int ke[kPlanKeep], kr[kPlanKeep];
-    if (kept) {
+    // Exclusive scans of the group sizes and of their tile counts (64 groups per wave, then the waves' totals), and the tiles.
+    auto scan = [&]() {
+        __syncthreads();
+        __shared__ int wsum[(MOE_MAX_EXPERTS + kWave) / kWave], wtiles[(MOE_MAX_EXPERTS + kWave) / kWave];
+        int sc_v = 0, sc_t = 0, sc_c = 0, sc_ct = 0;
+        const int lane = tid & (kWave - 1), wave = tid / kWave;
+        if (wave * kWave < G) {
+            sc_c = tid < G ? cnt[tid] : 0;
+            sc_ct = (sc_c + kTileM - 1) / kTileM;
+            sc_v = sc_c;
+            sc_t = sc_ct;
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int y = __shfl_up(sc_v, d), ty = __shfl_up(sc_t, d);
+                if (lane >= d) {
+                    sc_v += y;
+                    sc_t += ty;
+                }
+            }
+            if (lane == kWave - 1) {
+                wsum[wave] = sc_v;
+                wtiles[wave] = sc_t;
+            }
+        }
+        __syncthreads();
+        if (wave * kWave < G) {
+            int before = 0, tbefore = 0;
+            for (int w = 0; w < wave; ++w) {
+                before += wsum[w];
+                tbefore += wtiles[w];
+            }
+            if (tid < G) {
+                off[tid] = before + sc_v - sc_c;
+                toff[tid] = tbefore + sc_t - sc_ct;
+            }
+            if (tid == G - 1) {
+                off[G] = before + sc_v;
+                toff[G] = tbefore + sc_t;
+                ws.hdr[0] = tbefore + sc_t;
+            }
+        }
+        __syncthreads();
+        for (int g = tid; g <= G; g += kPlanThreads) {
+            ws.g_off[g] = off[g];
+            if (g < G) {
+                ws.g_slot[g] = slot[g];
+                for (int i = 0, t = toff[g]; t < toff[g + 1]; ++i, ++t) {
+                    ws.tile_g[t] = g;
+                    ws.tile_r0[t] = i * kTileM;
+                }
+            }
+        }
+    };
+    // Up to 16384 pairs: a thread's ids (1, 4 or 16) are loaded together and stay in registers with their ranks within
+    // their experts' groups (one load latency and one pass of LDS atomics, where a load per 1024 pairs and two passes took
+    // 25 us for 2048 tokens of top-8; sixteen ids where one would do, 4.1 us instead of 2.6 for 17 tokens).  More pairs:
+    // two passes, eight ids loaded together.
+    auto kept = [&](auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        int ke[N], kr[N];
 #pragma unroll
-        for (int u = 0; u < kPlanKeep; ++u) ke[u] = ids[min(tid + u * kPlanThreads, P - 1)];
+        for (int u = 0; u < N; ++u) ke[u] = ids[min(tid + u * kPlanThreads, P - 1)];
+        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kPlanKeep; ++u) {
+        for (int u = 0; u < N; ++u) {
             const int p = tid + u * kPlanThreads;
             ke[u] = p < P ? checked(ke[u], p) : -1;
             if (ke[u] >= 0) kr[u] = atomicAdd(&cnt[ke[u]], 1);
         }
+        scan();
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (ke[u] >= 0) ws.sorted[off[ke[u]] + kr[u]] = tid + u * kPlanThreads;
+    };
+    if (P <= kPlanThreads) {
+        kept(std::integral_constant<int, 1>{});
+    } else if (P <= 4 * kPlanThreads) {
+        kept(std::integral_constant<int, 4>{});
+    } else if (P <= kPlanKeep * kPlanThreads) {
+        kept(std::integral_constant<int, kPlanKeep>{});
     } else {
+        __syncthreads();
         for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
             int e[kPlanIds];
 #pragma unroll
@@ -140,64 +205,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const int32_
                 if (p < P && e[u] >= 0) atomicAdd(&cnt[e[u]], 1);
             }
         }
-    }
-    __syncthreads();
-    if (tid == 0) cnt[E] = has_shared ? T : 0;
-    __syncthreads();
-    // exclusive scans of the group sizes and of their tile counts: 64 groups per wave, then the waves' totals
-    __shared__ int wsum[(MOE_MAX_EXPERTS + kWave) / kWave], wtiles[(MOE_MAX_EXPERTS + kWave) / kWave];
-    int sc_v = 0, sc_t = 0, sc_c = 0, sc_ct = 0;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
-    if (wave * kWave < G) {
-        sc_c = tid < G ? cnt[tid] : 0;
-        sc_ct = (sc_c + kTileM - 1) / kTileM;
-        sc_v = sc_c;
-        sc_t = sc_ct;
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int y = __shfl_up(sc_v, d), ty = __shfl_up(sc_t, d);
-            if (lane >= d) {
-                sc_v += y;
-                sc_t += ty;
-            }
-        }
-        if (lane == kWave - 1) {
-            wsum[wave] = sc_v;
-            wtiles[wave] = sc_t;
-        }
-    }
-    __syncthreads();
-    if (wave * kWave < G) {
-        int before = 0, tbefore = 0;
-        for (int w = 0; w < wave; ++w) {
-            before += wsum[w];
-            tbefore += wtiles[w];
-        }
-        if (tid < G) {
-            off[tid] = before + sc_v - sc_c;
-            toff[tid] = tbefore + sc_t - sc_ct;
-        }
-        if (tid == G - 1) {
-            off[G] = before + sc_v;
-            toff[G] = tbefore + sc_t;
-            ws.hdr[0] = tbefore + sc_t;
-        }
-    }
-    __syncthreads();
-    for (int g = tid; g <= G; g += kPlanThreads) {
-        ws.g_off[g] = off[g];
-        if (g < G) {
-            ws.g_slot[g] = slot[g];
-            for (int i = 0, t = toff[g]; t < toff[g + 1]; ++i, ++t) {
-                ws.tile_g[t] = g;
-                ws.tile_r0[t] = i * kTileM;
-            }
-        }
-    }
-    if (kept) {
-#pragma unroll
-        for (int u = 0; u < kPlanKeep; ++u)
-            if (ke[u] >= 0) ws.sorted[off[ke[u]] + kr[u]] = tid + u * kPlanThreads;
-    } else {
+        scan();
         for (int p0 = tid; p0 < P; p0 += kPlanIds * kPlanThreads) {
             int e[kPlanIds];
 #pragma unroll

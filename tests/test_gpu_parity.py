@@ -1097,12 +1097,16 @@ def test_prefill_parity_small_ragged(dtype, shared):
 
 
 @pytest.mark.parametrize("T,E,k,H,I,dtype,shared", [(16384, 130, 1, 128, 128, synth.BF16, False),
+                                                     (512, 64, 2, 128, 128, synth.BF16, True),
+                                                     (1025, 65, 1, 128, 128, synth.INT4G128, False),
+                                                     (1024, 256, 4, 128, 128, synth.BF16, True),
+                                                     (4097, 63, 1, 128, 128, synth.INT4G128, False),
                                                      (3000, 256, 6, 128, 128, synth.INT4G128, True),
                                                      (21, 12, 3, 2176, 128, synth.INT4G128, True)])
 def test_prefill_plan_and_reduction_edges(T, E, k, H, I, dtype, shared):
-    """As many pairs as the grouping block keeps in registers (16384) and more (two passes), expert counts that
-    are no multiple of a wave and 256 + the shared one, and a reduction range of 17 rounds (scales and group sums
-    are staged 16 rounds at a time).  Sampled tokens against the oracle, the prefill tolerance."""
+    """As many pairs as the grouping block keeps in registers, one, four or 16 per thread (1024, 4096, 16384), and one more
+    than each (beyond the last: two passes), expert counts that are no multiple of a wave and 256 + the shared one, and a
+    reduction range of 17 rounds (scales and group sums are staged 16 rounds at a time).  Sampled tokens against the oracle, the prefill tolerance."""
     wl = synth.Workload("prefill-edges", H=H, E=E, k=k, I=I, dtype=dtype, router_dtype=synth.F32, shared=shared,
                         cfg_id=500 + E + dtype)
     ex, sh = _experts(wl)
