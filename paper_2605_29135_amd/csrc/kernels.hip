@@ -347,14 +347,14 @@ __global__ __launch_bounds__(kBlock) void rmsnorm_rows_kernel(const float *x, in
 // logits[t, e] = sum_i W[e, i] h[t, i] (+ bias[t, e]); W bf16 [E x H], H % 32 == 0; h = x, or with NORM
 // h = x / sqrt(mean(x^2) + eps), applied to the sums (a row's factor is known only when the row has been read).
 // A block takes 16 RG tokens x 16 CB experts; its 8 waves split the H range into contiguous slices of 32-wide k
-// steps, each wave issuing the loads of ROUND steps before its first product (lane (lr = l % 16, lg = l / 16)
+// steps, each wave issuing the loads of ROUND steps before their first product (lane (lr = l % 16, lg = l / 16)
 // supplies x[t0 + 16i + lr][k + 8lg .. +7] and W[e0 + 16j + lr][k + 8lg .. +7]), and the waves' partial tiles are
 // summed through LDS in wave order.  With NORM the blocks of a token row share the columns of h_out (may be NULL).
 // Few tokens take 16 x 32 tiles (more blocks); many take 32 x 64 ones, since the launch is then bound by what the
-// blocks read from L2: 2048 tokens x 256 experts, H 2048: 268 MB in 1024 blocks 38.8 us (and 7.0 us for a launch
-// that normalised the rows), 134 MB in 256 blocks 27 us with the norm.  At 262144 logits (512 narrow
-// blocks, one round of two per compute unit) narrow tiles are the faster ones (19 against 25 us), at 524288 wide
-// ones (27 against 33).
+// blocks read from L2 (2048 tokens x 256 experts, H 2048: 268 MB in 1024 blocks, 134 MB in 256 blocks).  Whole call with
+// norm and top-k, H 2048, us: 1000 x 256 (512 narrow blocks, one round of two per compute unit) 23.3 narrow, 28.0 wide;
+// 2048 x 130 31.9 and 29.8; 2048 x 256 38.1 and 31.2.  Rounds of two steps: of eight (narrow) or four (wide) 1 to 6 %
+// slower where blocks fill the chip, and 13.2 against 8.2 for 16 tokens at H 512, whose waves have two steps each.
 constexpr int kRouterKWaves = 8;   // waves per block, each over its own slice of the H range
 template <int RG, int CB, int ROUND, bool NORM>
 __global__ __launch_bounds__(kRouterKWaves * kWave) void router_mfma_kernel(const float *__restrict__ x,
@@ -399,10 +399,15 @@ __global__ __launch_bounds__(kRouterKWaves * kWave) void router_mfma_kernel(cons
 #pragma unroll
             for (int j = 0; j < CB; ++j) wv[r][j] = *reinterpret_cast<const u32x4 *>(wr[j] + k);
         }
-        // A fence over every loaded register: the compiler cannot move a load past it, so the round's loads
-        // are in flight together and the wave waits once (left to itself it interleaves each step's loads with
-        // the previous step's products, one load latency per step).
-        asm volatile("" ::: "memory");
+        // Every loaded register passes through an empty asm: no load moves past it, so the round's loads are in flight
+        // together and the wave waits once per round.
+#pragma unroll
+        for (int r = 0; r < ROUND; ++r) {
+#pragma unroll
+            for (int i = 0; i < RG; ++i) asm volatile("" : "+v"(xv[r][i][0]), "+v"(xv[r][i][1])::"memory");
+#pragma unroll
+            for (int j = 0; j < CB; ++j) asm volatile("" : "+v"(wv[r][j])::"memory");
+        }
 #pragma unroll
         for (int r = 0; r < ROUND; ++r) {
             // a step past the wave's slice multiplies zero weights (no branch around the products)
@@ -1332,8 +1337,8 @@ hipError_t launch_router_logits(const float *x, const void *w, int w_dtype, int 
             router_mfma_kernel<RG, CB, ROUND, false><<<g, kRouterKWaves * kWave, 0, s>>>(x, wb, T, H, E, bias, logits, nullptr); \
         return finish();                                                                                               \
     }
-        if (size_t(T) * E > kRouterWide) ROUTER_MFMA(2, 4, 4)
-        ROUTER_MFMA(1, 2, 8)
+        if (size_t(T) * E > kRouterWide) ROUTER_MFMA(2, 4, 2)
+        ROUTER_MFMA(1, 2, 2)
 #undef ROUTER_MFMA
     }
     const dim3 grid((E + 3) / 4, T);
