@@ -473,7 +473,16 @@ __global__ __launch_bounds__(kRouterKWaves * kWave) void router_mfma_kernel(cons
 #pragma unroll
             for (int wv = 0; wv < kRouterKWaves; ++wv) v += red[wv][i][j][q][lane];
             const int tr = 16 * i + 4 * lg + q, t = t0 + tr, e = e0 + 16 * (2 * h + j) + lr;
-            if constexpr (NORM) v *= inv_rms[tr];
+            if constexpr (NORM) {
+                const float f = inv_rms[tr];
+                v *= f;
+                // products of values not yet normalised can overflow where the normalised ones do not: formed again
+                if (!(fabsf(v) < INFINITY) && t < T && e < E) {
+                    v = 0.f;
+#pragma unroll 1
+                    for (int c = 0; c < H; ++c) v = fmaf(bf16_bits_to_float(w[size_t(e) * H + c]), x[size_t(t) * H + c] * f, v);
+                }
+            }
             if (t < T && e < E) logits[size_t(t) * E + e] = v + (bias ? bias[size_t(t) * E + e] : 0.f);
         }
     }

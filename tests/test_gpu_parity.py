@@ -130,6 +130,29 @@ def test_route_normalises_in_place():
     assert normwise(xd.cpu().numpy(), oracle.rmsnorm(x)) <= 1e-6 and normwise(h.cpu().numpy(), oracle.rmsnorm(x)) <= 1e-6
 
 
+def test_route_normalised_range():
+    """Rows whose raw products overflow and whose normalised ones do not (hidden values near the largest float, whose mean
+    square is infinite and normalised row zero; large ones against a router row near 1e30), in calls of sixteen tokens and
+    more: the logits are those of calls of fewer tokens, which normalise first.  Sums of 512 fp32 terms: 1e-5."""
+    rng = np.random.default_rng(9)
+    T, E, H = 20, 40, 512
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    x[3] = 3.39e38 * np.sign(x[3])
+    x[7] *= np.float32(1e16)
+    w = 0.02 * rng.standard_normal((E, H)).astype(np.float32)
+    w[11] *= np.float32(1e32)
+    wr = dev(w).to(torch.bfloat16)
+    xd, few = dev(x), []
+    many = moe.moe_route_topk(xd, wr, synth.BF16, 4, rmsnorm=True, x_norm=torch.empty_like(xd))[0].cpu().numpy()
+    for t in (0, 10):
+        few.append(moe.moe_route_topk(xd[t:t + 10], wr, synth.BF16, 4, rmsnorm=True)[0].cpu().numpy())
+    moe.moe_sync_check()
+    few = np.concatenate(few).astype(np.float64)
+    assert (many[3] == 0).all() and np.isfinite(few).all()
+    rms = np.sqrt((few ** 2).mean(0))  # by expert: router row 11 is 1e32 times the others
+    assert (np.abs(many - few) <= 1e-5 * rms).all()
+
+
 @pytest.mark.parametrize("E,k", [(16, 16), (256, 1), (256, 16), (64, 3), (130, 5)])
 def test_route_ties_and_edge_k(E, k):
     rng = np.random.default_rng(E + k)
