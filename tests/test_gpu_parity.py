@@ -501,6 +501,45 @@ def test_ffn_invalid_ids_raise_and_contribute_nothing():
     assert ei.value.code == -8
 
 
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("T", [2, 6, 16])
+@pytest.mark.parametrize("dtype,H", [(synth.F32, 256), (synth.BF16, 1024), (synth.INT4G128, 256)])
+def test_ffn_batch_bad_pairs(dtype, H, T, shared):
+    """Several tokens with ids below 0 and from E on, and an expert without a slot that several tokens name: the flag of
+    each, and outputs that hold the other pairs alone; also where no routed pair is valid.  (f32, and 2 tokens without
+    the shared expert: one wave per row pair; the others: the matrix cores.)  Bounds as for valid ids."""
+    wl = synth.Workload("bad pairs", H=H, E=6, k=4, I=256, dtype=dtype, router_dtype=synth.F32, shared=shared,
+                        cfg_id=650 + dtype)
+    ex, sh = _experts(wl)
+    rng = np.random.default_rng(T + dtype)
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    w = rng.random((T, 4)).astype(np.float32)
+    good = np.argsort(rng.random((T, wl.E)), axis=1)[:, :4].astype(np.int32)
+    slot_of = np.arange(wl.E, dtype=np.int32)
+    slot_of[2] = -1  # expert 2 has none
+    outside = good.copy()
+    outside[0, 1], outside[T - 1, 3], outside[T // 2, 0] = -1, wl.E, 2 ** 31 - 1
+    only_bad = np.where(rng.random((T, 4)) < 0.5, -7, wl.E + 3).astype(np.int32)
+    bound = 1e-3 if dtype == synth.INT4G128 else 1e-5
+    for ids, table, code in ((outside, None, -2), (np.where(good == 5, 2, good), slot_of, -8), (only_bad, None, -2),
+                             (np.full((T, 4), 2, np.int32), slot_of, -8)):
+        y = moe.moe_expert_ffn_grouped(dev(x), dev(ids), dev(w), dev(ex.reshape(-1)), wl.expert_bytes, dtype, wl.I, wl.E,
+                                       slot_of=None if table is None else dev(table),
+                                       shared_w=None if sh is None else dev(sh))
+        if (ids == 2).any() or table is None:
+            with pytest.raises(moe.MoeError) as ei:
+                moe.moe_sync_check()
+            assert ei.value.code == code
+        ok = (ids >= 0) & (ids < wl.E) & ((table is None) | (ids != 2))
+        ref = oracle.moe_ffn(x, np.where(ok, ids, 0), np.where(ok, w, 0).astype(np.float64), ex, H, wl.I, dtype, sh)
+        got = y.cpu().numpy()
+        for t in range(T):
+            if ok[t].any() or shared:
+                assert normwise(got[t], ref[t]) <= bound
+            else:
+                assert (got[t] == 0).all()
+
+
 def test_combine_parity():
     rng = np.random.default_rng(3)
     T, k, H = 5, 8, 2048
