@@ -165,7 +165,7 @@ int moe_expert_ffn_grouped(const float *x, int T, int H, int I, int E, int k, co
                     moe::ffn_workspace_bytes(T, k, I));
     int *eflags = moe::device_error_flags();
     if (!eflags) return fail(MOE_ERR_HIP, "device error flags unavailable");
-    const moe::FfnWorkspace ws = moe::ffn_workspace(workspace, T, k, I);
+    const moe::FfnWorkspace ws = moe::ffn_workspace(workspace);
     return finish_launch(moe::launch_expert_ffn(x, T, H, I, E, k, ids, weights, slot_of, pool, expert_bytes,
                                                 w_dtype, shared_w, y_out, flags & MOE_ACCUMULATE, ws, eflags,
                                                 static_cast<hipStream_t>(stream)),

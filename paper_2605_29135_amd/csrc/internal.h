@@ -23,7 +23,7 @@ struct FfnWorkspace {
     float *act;       // [(T*k + T) x I] SwiGLU activations, one row per (token, rank) pair + shared
 };
 size_t ffn_workspace_bytes(int T, int k, int I);
-FfnWorkspace ffn_workspace(void *base, int T, int k, int I);
+FfnWorkspace ffn_workspace(void *base);
 
 // Kernel launchers (all asynchronous on `s`).  Shapes are validated by the caller.
 hipError_t launch_router_logits(const float *x, const void *w, int w_dtype, int T, int H, int E,

@@ -570,27 +570,25 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
     int s_ld = 0, nf_ld = 0, fslot = -1;
     long long fsrc = 0;
     bool dev_slot = false;
-    {
-        clk = plan.fill.n ? plan.fill.clk : nullptr;
-        if (plan.fill.n && g == int(gridDim.y) - 1) {
-            const bool busy = int(blockIdx.x) < min(plan.fill.n[0], MOE_MAX_TOPK) * plan.fill.slices;
-            const unsigned long long t0 = clk && busy ? devres::clk_now() : 0ull;
-            copy_down_parts(plan.fill, expert_bytes);
-            if (t0) devres::clk_record_fill(clk, t0, devres::clk_now());
-            return;
-        }
-        dev_slot = g < k && !plan.n;
-        if (dev_slot) {
-            // (the block-uniform words go through vector loads: earlier kernels on the stream wrote them)
-            if (plan.fill.n) {
-                nf_ld = load_stream_word(plan.fill.n);
-                if (lane < min(E, MOE_MAX_TOPK)) {  // (the fill list holds E entries)
-                    fslot = plan.fill.slot[lane];
-                    fsrc = plan.fill.src[lane];
-                }
+    clk = plan.fill.n ? plan.fill.clk : nullptr;
+    if (plan.fill.n && g == int(gridDim.y) - 1) {
+        const bool busy = int(blockIdx.x) < min(plan.fill.n[0], MOE_MAX_TOPK) * plan.fill.slices;
+        const unsigned long long t0 = clk && busy ? devres::clk_now() : 0ull;
+        copy_down_parts(plan.fill, expert_bytes);
+        if (t0) devres::clk_record_fill(clk, t0, devres::clk_now());
+        return;
+    }
+    dev_slot = g < k && !plan.n;
+    if (dev_slot) {
+        // (the block-uniform words go through vector loads: earlier kernels on the stream wrote them)
+        if (plan.fill.n) {
+            nf_ld = load_stream_word(plan.fill.n);
+            if (lane < min(E, MOE_MAX_TOPK)) {  // (the fill list holds E entries)
+                fslot = plan.fill.slot[lane];
+                fsrc = plan.fill.src[lane];
             }
-            s_ld = load_stream_word((plan.rank_slot ? plan.rank_slot : ids) + g);
         }
+        s_ld = load_stream_word((plan.rank_slot ? plan.rank_slot : ids) + g);
     }
     if (!STAGE_X && !STAGE_XF && i >= I) return;  // when x is staged, every wave joins the block's staging below
     float xv[STAGE_X || STAGE_XF ? 1 : NCH][EPC];
@@ -633,54 +631,52 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
             xa[r][1] = in ? xt4[2 * f + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
-    {
-        // (the loaded values pass through an empty asm after the x loads, so that no use of them -- and no
-        // wait for them -- is scheduled before x is in flight)
-        if (dev_slot) asm volatile("" : "+v"(s_ld), "+v"(nf_ld), "+v"(fslot), "+v"(fsrc)::"memory");
-        if (g < k && plan.n) {
-            // slots known on the host: no device lookups.  Selected with the block-uniform rank so that
-            // the offsets stay argument (scalar) loads rather than one indexed load before the weights.
-            long long off = plan.off[0];
+    // (the loaded values pass through an empty asm after the x loads, so that no use of them -- and no
+    // wait for them -- is scheduled before x is in flight)
+    if (dev_slot) asm volatile("" : "+v"(s_ld), "+v"(nf_ld), "+v"(fslot), "+v"(fsrc)::"memory");
+    if (g < k && plan.n) {
+        // slots known on the host: no device lookups.  Selected with the block-uniform rank so that
+        // the offsets stay argument (scalar) loads rather than one indexed load before the weights.
+        long long off = plan.off[0];
 #pragma unroll
-            for (int j = 1; j < MOE_MAX_TOPK; ++j)
-                if (g == j) off = plan.off[j];
-            if (off < 0) return;  // a rank the host tier computes
-            blob = pool + off;
-        } else if (dev_slot) {
-            int s;
-            if (plan.rank_slot) {  // the device lookup's slot for this rank (it flagged bad ids itself)
-                s = s_ld;
-            } else {
-                const int e = s_ld;
-                if (e < 0 || e >= E) {
-                    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, kErrRange);
-                    return;
-                }
-                s = slot_of ? slot_of[e] : e;
-                asm volatile("" : "+v"(s));  // (the wait for this dependent load stays on this path)
-            }
-            if (s < 0) {
-                if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, kErrNotResident);
+        for (int j = 1; j < MOE_MAX_TOPK; ++j)
+            if (g == j) off = plan.off[j];
+        if (off < 0) return;  // a rank the host tier computes
+        blob = pool + off;
+    } else if (dev_slot) {
+        int s;
+        if (plan.rank_slot) {  // the device lookup's slot for this rank (it flagged bad ids itself)
+            s = s_ld;
+        } else {
+            const int e = s_ld;
+            if (e < 0 || e >= E) {
+                if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, kErrRange);
                 return;
             }
-            blob = pool + size_t(s) * expert_bytes;
-            if (plan.fill.n) {
-                // the lanes holding a fill of this slot (at most one: a step fills a slot once)
-                const unsigned long long m = __ballot(lane < min(nf_ld, MOE_MAX_TOPK) && fslot == s);
-                if (m) {
-                    const int f = __ffsll((long long)m) - 1;
-                    const unsigned lo = __builtin_amdgcn_readlane(unsigned(fsrc), f);
-                    const unsigned hi = __builtin_amdgcn_readlane(unsigned((unsigned long long)fsrc >> 32), f);
-                    dst = plan.fill.pool + size_t(s) * expert_bytes;
-                    blob = plan.fill.host + (long long)(((unsigned long long)hi << 32) | lo);
-                    if (int(blockIdx.x) >= plan.fill.blocks) return;
-                    istride = plan.fill.blocks * (kBlock / kWave);
-                    if (clk) t_fill = devres::clk_now();
-                }
-            }
-        } else {
-            blob = shared_w;
+            s = slot_of ? slot_of[e] : e;
+            asm volatile("" : "+v"(s));  // (the wait for this dependent load stays on this path)
         }
+        if (s < 0) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, kErrNotResident);
+            return;
+        }
+        blob = pool + size_t(s) * expert_bytes;
+        if (plan.fill.n) {
+            // the lanes holding a fill of this slot (at most one: a step fills a slot once)
+            const unsigned long long m = __ballot(lane < min(nf_ld, MOE_MAX_TOPK) && fslot == s);
+            if (m) {
+                const int f = __ffsll((long long)m) - 1;
+                const unsigned lo = __builtin_amdgcn_readlane(unsigned(fsrc), f);
+                const unsigned hi = __builtin_amdgcn_readlane(unsigned((unsigned long long)fsrc >> 32), f);
+                dst = plan.fill.pool + size_t(s) * expert_bytes;
+                blob = plan.fill.host + (long long)(((unsigned long long)hi << 32) | lo);
+                if (int(blockIdx.x) >= plan.fill.blocks) return;
+                istride = plan.fill.blocks * (kBlock / kWave);
+                if (clk) t_fill = devres::clk_now();
+            }
+        }
+    } else {
+        blob = shared_w;
     }
     const size_t rb = row_bytes_of(DT, H);
     for (bool first = true;; first = false) {
@@ -775,44 +771,42 @@ __global__ __launch_bounds__(kBlock) void gateup_kernel(
             }
         }
     }
-    {
-        float ga = 0.f, ua = 0.f;
+    float ga = 0.f, ua = 0.f;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            if constexpr (STAGE_X) {
-                ga += ldexpf((chunk_dot_i4h(wg[c], xq[c]) - xbias[c]) * sg[c], xsh_[c]);
-                ua += ldexpf((chunk_dot_i4h(wu[c], xq[c]) - xbias[c]) * su[c], xsh_[c]);
+    for (int c = 0; c < NCH; ++c) {
+        if constexpr (STAGE_X) {
+            ga += ldexpf((chunk_dot_i4h(wg[c], xq[c]) - xbias[c]) * sg[c], xsh_[c]);
+            ua += ldexpf((chunk_dot_i4h(wu[c], xq[c]) - xbias[c]) * su[c], xsh_[c]);
+        } else {
+            float xl[EPC];  // this chunk's x: from LDS (STAGE_XF) or the wave's registers
+            if constexpr (STAGE_XF) {
+                extern __shared__ float4 xsf[];
+                const int col0 = (c * kWave + lane) * EPC;
+#pragma unroll
+                for (int h = 0; h < EPC / 4; ++h) {
+                    const float4 v = (FULL || col0 < H) ? xsf[col0 / 4 + h] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    xl[4 * h] = v.x;
+                    xl[4 * h + 1] = v.y;
+                    xl[4 * h + 2] = v.z;
+                    xl[4 * h + 3] = v.w;
+                }
             } else {
-                float xl[EPC];  // this chunk's x: from LDS (STAGE_XF) or the wave's registers
-                if constexpr (STAGE_XF) {
-                    extern __shared__ float4 xsf[];
-                    const int col0 = (c * kWave + lane) * EPC;
 #pragma unroll
-                    for (int h = 0; h < EPC / 4; ++h) {
-                        const float4 v = (FULL || col0 < H) ? xsf[col0 / 4 + h] : make_float4(0.f, 0.f, 0.f, 0.f);
-                        xl[4 * h] = v.x;
-                        xl[4 * h + 1] = v.y;
-                        xl[4 * h + 2] = v.z;
-                        xl[4 * h + 3] = v.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int h = 0; h < EPC; ++h) xl[h] = xv[STAGE_XF ? 0 : c][h];
-                }
-                float dg = chunk_dot<DT>(wg[c], xl), du = chunk_dot<DT>(wu[c], xl);
-                if constexpr (DT == INT4) {
-                    dg *= sg[c];
-                    du *= su[c];
-                }
-                ga += dg;
-                ua += du;
+                for (int h = 0; h < EPC; ++h) xl[h] = xv[STAGE_XF ? 0 : c][h];
             }
+            float dg = chunk_dot<DT>(wg[c], xl), du = chunk_dot<DT>(wu[c], xl);
+            if constexpr (DT == INT4) {
+                dg *= sg[c];
+                du *= su[c];
+            }
+            ga += dg;
+            ua += du;
         }
-        ga = wave_sum(ga);
-        ua = wave_sum(ua);
-        // the combine weight is folded in here
-        if (lane == 0) act[size_t(g) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
     }
+    ga = wave_sum(ga);
+    ua = wave_sum(ua);
+    // the combine weight is folded in here
+    if (lane == 0) act[size_t(g) * I + i] = wp * (ga * __builtin_amdgcn_rcpf(1.f + __expf(-ga)) * ua);
     if (!istride) break;  // block-uniform; no barrier follows the first pass
     i += istride;
     if (i >= I) break;
@@ -1299,7 +1293,7 @@ size_t ffn_workspace_bytes(int T, int k, int I) {
     return act + grp;
 }
 
-FfnWorkspace ffn_workspace(void *base, int, int, int) {
+FfnWorkspace ffn_workspace(void *base) {
     FfnWorkspace w;
     w.act = static_cast<float *>(base);
     return w;
@@ -1468,7 +1462,7 @@ hipError_t launch_expert_ffn(const float *x, int T, int H, int I, int E, int k, 
         launched = true;                                                                            \
     }
     hipError_t e = hipSuccess;
-    if (!launched && !one) {  // 2 to 16 tokens: on the matrix cores
+    if (!launched && !one) {  // 2 to 16 tokens: batch_ffn.hip
         e = launch_batch_gateup(x, T, H, I, E, k, ids, weights, slot_of, pl, expert_bytes, dtype, sw, ws.act, err_flags, s);
         launched = true;
     }

@@ -369,7 +369,7 @@ int enqueue_decode(moe_stack *s, int step, float *x, int T, const float *logit_b
     int *eflags = moe::device_error_flags();
     if (!eflags) return moe::fail(MOE_ERR_HIP, "device error flags unavailable");
     const auto &d = s->d;
-    const moe::FfnWorkspace ws = moe::ffn_workspace(s->ws, T, d.k, d.I);
+    const moe::FfnWorkspace ws = moe::ffn_workspace(s->ws);
     s->recalled = -1;
     if (s->attn && (T != 1 || s->attn_pos >= s->ad.max_pos))
         return moe::fail(MOE_ERR_INVALID_ARG, T != 1 ? "stack step: an attention block decodes one token per step"
@@ -632,7 +632,7 @@ int moe_stack_kernel_time(moe_stack *s, int which, int n, void *stream, double *
     if (!eflags) return moe::fail(MOE_ERR_HIP, "device error flags unavailable");
     const auto &d = s->d;
     const int L = d.n_layers, T = s->last[0].T;
-    const moe::FfnWorkspace ws = moe::ffn_workspace(s->ws, T, d.k, d.I);
+    const moe::FfnWorkspace ws = moe::ffn_workspace(s->ws);
     // One token with device lookups: each layer's slots, as its lookup left them, become that layer's
     // launch plan, so that every re-launch reads the slots the step read (later layers may have evicted
     // some of them since, which only changes the bytes read, not where or how many).
