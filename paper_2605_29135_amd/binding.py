@@ -149,9 +149,13 @@ def _dev(t, name: str, dtype=None):
 
 
 def _stream(stream):
-    if stream is None:  # the current device's stream as the raw handle (no Stream object per call)
+    if stream is None:  # the current device's stream as the raw handle (no Stream object per call), where torch has that
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        device = torch.cuda.current_device()
+        try:
+            return torch._C._cuda_getCurrentRawStream(device)
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

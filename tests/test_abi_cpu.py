@@ -247,3 +247,18 @@ def test_opt_fills_rejects_bad_traces():
         moe.moe_opt_fills([[1, 1]], 3, 2)
     assert ei.value.code == -1
     assert moe.moe_opt_fills([], 3, 2) == 0
+
+
+def test_stream_handle_where_torch_has_no_raw_getter(monkeypatch):
+    """The current stream's handle comes from torch's raw getter or, where a torch has none, from its Stream object; a
+    given stream is taken as it is."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=71))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 40 + device, raising=False)
+    assert binding._stream(None) == 43
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._stream(None) == 71
+    assert binding._stream(types.SimpleNamespace(cuda_stream=9)) == 9 and binding._stream(12) == 12
