@@ -175,8 +175,8 @@ __device__ __forceinline__ void find_groups(BatchGroups &G, int P, int E, const 
 // that every product is exact and only the order of the fp32 sums differs from a row-wise dot product.
 // Bound by HBM (large batches) or by the latency of a few items per block (small ones).  Measured against one
 // wave per row pair that took its expert's tokens one after the other, behind a launch that grouped the pairs:
-// 16 tokens, H 2048, I 512, 256 Zipf-routed bf16 experts + shared (260 MB): 54 + 16 -> 56 us, 4.6 TB/s; 5
-// tokens on int4 experts of the same shape (31 MB): 31 + 6 -> 18 us.
+// 16 tokens, H 2048, I 512, 256 Zipf-routed bf16 experts + shared (251 MB): 54 + 16 -> 53 us, 4.7 TB/s; 5
+// tokens on int4 experts of the same shape (31 MB): 31 + 6 -> 19 us.
 template <int DT, int CS, bool ONE>  // ONE: a single pass over the reduction range
 __global__ __launch_bounds__(kBatchBlock, 2) void batch_gateup_kernel(
     const float *__restrict__ x, int T, int H, int I, int E, int k, const int32_t *__restrict__ ids,

@@ -243,7 +243,7 @@ struct Round {
 // round's loads and the unpacking more than by the matrix cores: so A rows are staged by consecutive threads (a load
 // instruction touches 8 cache lines instead of 32), and the scales and group sums of 16 rounds are staged at once
 // instead of five small loads per round; and each row's token is divided out once per row, not per thread and load.
-// 2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> about 161 us (155 with accumulators that start
+// 2048 tokens, top-8 of 256 experts + shared, H 2048, I 512: 188 -> 158 us (155 with accumulators that start
 // from -136 S_m, which round otherwise than the down GEMM's fold: outputs 1.2e-4 apart, the same error).
 // Measured and not kept: weights two rounds ahead (spills: 227 us), 80- and 96-row tiles of 128 columns in two or
 // three blocks per compute unit (254-270 us), products and unpacking interleaved by scheduling groups (222 us), the
