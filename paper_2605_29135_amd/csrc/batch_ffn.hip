@@ -504,7 +504,7 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
 
 // Which kernel: one wave per row pair (true) or the matrix cores.  The matrix cores win where many of a wave's tokens
 // would follow one another; their cost is the search before the first load and steps that fill no whole pass.  Row
-// pairs / matrix cores, us for the whole FFN, each with its neighbours at other T on the same side:
+// pairs / matrix cores, us for the whole FFN:
 // bf16, by the tokens per expert T k / E and by T (the most chosen experts' tokens, and the shared expert's T).  H 2048,
 // I 768, top-8 of 128: 55 / 60 at 6 tokens, 92 / 93 at 12, 117 / 113 at 16 (T k / E = 1); top-4 of 16: 28.1 / 30.6 at
 // 6 (1.5), 39 / 37 at 10 (2.5); H 1024, I 1536, top-4 of 32: 41 / 43 at 10 (1.25), 56 / 54 at 16 (2).  With a shared
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(kBlock) void batch_gateup_rows_kernel(
 // Beyond H 2048 the matrix cores would read the tokens anew in every pass (H 2560, I 768, 16 tokens: 140 / 285).
 // int4, by blocks times the tokens that follow one another, since a row pair's products cost several times the loads
 // there: H 2048, I 128, top-1 of 16: 12.5 / 14.9 at 6 tokens (1152), 20.8 / 19.4 at 12 (4608); H 6144: 18.9 / 26.1
-// at 4 (512), 42 / 44 at 12; H 2176, I 256, top-2 of 16: 15.3 / 17.3 at 4 (2048), 20 / 19.2 at 6 (4608); with a shared
+// at 4 (512), 42 / 44 at 12 (4608, where the line costs 4 %); H 2176, I 256, top-2 of 16: 15.3 / 17.3 at 4 (2048), 20 / 19.2 at 6 (4608); with a shared
 // expert H 4096, I 128, top-2 of 8: 14.6 / 18.5 at 3 (1728), 24 / 22 at 5 (4800).
 bool rows_faster(int T, int H, int I, int E, int k, int dtype, bool shared) {
     if (dtype == F32) return true;
